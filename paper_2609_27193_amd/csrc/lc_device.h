@@ -19,6 +19,17 @@ __device__ __forceinline__ u32x4 ld_nt(const u32x4* p) {
   return __builtin_nontemporal_load((const g_u32x4*)p);
 }
 __device__ __forceinline__ void st_nt(u32x4* p, u32x4 v) { __builtin_nontemporal_store(v, (g_u32x4*)p); }
+// The same at any 2- or 4-byte address: gfx950 takes unaligned global accesses.
+typedef u32x4 __attribute__((aligned(2))) u32x4_any2;
+typedef u32x4 __attribute__((aligned(4))) u32x4_any4;
+typedef __attribute__((address_space(1))) u32x4_any2 g_u32x4_any2;
+typedef __attribute__((address_space(1))) u32x4_any4 g_u32x4_any4;
+template <uint32_t ESZ>
+__device__ __forceinline__ u32x4 ld_any(const uint8_t* p) {
+  if constexpr (ESZ == 2) return __builtin_nontemporal_load((const g_u32x4_any2*)p);
+  else return __builtin_nontemporal_load((const g_u32x4_any4*)p);
+}
+__device__ __forceinline__ void st_any4(uint8_t* p, u32x4 v) { __builtin_nontemporal_store(v, (g_u32x4_any4*)p); }
 
 // bf16 -> fp32 is exact: the bf16 bits are the top half of the fp32 bits.
 __device__ __forceinline__ float bf_lo(uint32_t x) { return __uint_as_float(x << 16); }
@@ -28,6 +39,10 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) u32x2 g_u32x2;
 __device__ __forceinline__ u32x2 ld_nt2(const u32x2* p) { return __builtin_nontemporal_load((const g_u32x2*)p); }
 __device__ __forceinline__ void st_nt2(u32x2* p, u32x2 v) { __builtin_nontemporal_store(v, (g_u32x2*)p); }
+typedef u32x2 __attribute__((aligned(2))) u32x2_any2;
+typedef __attribute__((address_space(1))) u32x2_any2 g_u32x2_any2;
+__device__ __forceinline__ u32x2 ld_any2(const uint8_t* p) { return __builtin_nontemporal_load((const g_u32x2_any2*)p); }
+__device__ __forceinline__ void st_any2(uint8_t* p, u32x2 v) { __builtin_nontemporal_store(v, (g_u32x2_any2*)p); }
 
 // Full tiles (a whole score chunk or copy piece) go through buffer resources
 // built from the tile's base, which is uniform per block: the descriptor sits

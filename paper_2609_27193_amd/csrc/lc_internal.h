@@ -74,14 +74,47 @@ constexpr uint32_t kSelectThreads = 256;
 // device's limits leave no such size).
 uint32_t occupancy_lds(uint32_t blocks_per_cu);
 
+// A segment may start at any element, as the pieces of a ZeRO-3 rank do.  Its
+// first `head` elements run up to a 128-byte line of one of its arrays; the
+// chunks' tiles follow from there, so every tile starts on a line whatever the
+// segment starts on, and the first chunk holds the head beside its tile.  The
+// segment has ceil(numel / chunk elements) chunks whatever its head; with a
+// head, the last of them may hold no element.  Each kernel's head is of the
+// array whose stores weigh most: a store that starts inside a line leaves two
+// partial lines where a block ends (measured on one 160 M element segment 16 B
+// past a line: ACCUM score 189 -> 160 us, AdamW 1040 -> 818 us, SGD 469 -> 360
+// us), an unaligned load costs a few percent.
+constexpr uint32_t kLineBytes = 128u;
+inline uint16_t seg_head(uint64_t addr, uint32_t esz) {
+  return static_cast<uint16_t>((kLineBytes - addr % kLineBytes) % kLineBytes / esz);
+}
+
+// How the score kernel reads a segment's vectors and adds up their terms.
+enum ScoreForm : uint16_t {
+  kScorePairs = 0,    // w and s 16-B aligned: 16-B vectors, summed pairwise in fp32
+  kScoreWide = 1,     // w and s alike modulo 16: aligned vectors behind the head, each term added in fp64
+  kScoreWideAny = 2,  // w at any element against s: unaligned loads of w, each term added in fp64
+};
+
 // One segment as the score kernel sees it.
 struct ScoreSeg {
   uint64_t w;            // device address of the weights
   uint64_t s;            // device address of the shadow
   uint64_t numel;
   uint32_t chunk_begin;  // global index of the segment's first chunk
-  uint32_t vec_ok;       // w and s both 16-B aligned
+  uint16_t form;         // ScoreForm
+  uint16_t head;         // elements before the first tile
 };
+inline ScoreSeg score_seg(uint64_t w, uint64_t s, uint64_t numel, uint32_t esz, uint32_t chunk_begin) {
+  ScoreSeg g;
+  g.w = w;
+  g.s = s;
+  g.numel = numel;
+  g.chunk_begin = chunk_begin;
+  g.form = w % 16 == 0 && s % 16 == 0 ? kScorePairs : w % 16 == s % 16 ? kScoreWide : kScoreWideAny;
+  g.head = seg_head(s ? s : w, esz);
+  return g;
+}
 
 // One block of a layer record: one array (W, master, m or v) of one segment.
 struct CopyUnit {
@@ -95,6 +128,14 @@ struct CopyUnit {
   uint32_t pad;
 };
 
+// How the optimizer kernels read a segment's groups of four elements and add
+// up their drift terms.
+enum OptForm : uint16_t {
+  kOptPairs = 0,  // every array group-aligned at element 0: summed pairwise in fp32 (if the gradient is, too)
+  kOptWide = 1,   // every array group-aligned behind the head: each term added in fp64
+  kOptAny = 2,    // arrays at any element against each other: unaligned accesses, each term added in fp64
+};
+
 // One segment as the optimizer kernels see it (static part).
 struct OptSeg {
   uint64_t w;            // weights (bf16 or fp32)
@@ -103,14 +144,15 @@ struct OptSeg {
   uint64_t v;            // fp32 Adam second moment (AdamW only)
   uint64_t numel;
   uint32_t chunk_begin;  // same chunks as the score kernel
-  uint32_t vec_ok;       // master/m/v 16-B aligned and weights aligned to 4 elements
+  uint16_t form;         // OptForm
+  uint16_t head;         // elements before the first tile
 };
 
 // Per-call part: gradient address and weight-decay flag of each segment.
 struct GradSeg {
   uint64_t grad;
   uint32_t decay;
-  uint32_t vec_ok;  // gradient aligned to 4 elements
+  uint32_t vec_ok;  // gradient aligned to 4 elements at element 0
 };
 
 // fp32 scalars of one AdamW step, formed in fp64 on the host and rounded once.

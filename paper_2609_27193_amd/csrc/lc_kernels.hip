@@ -65,11 +65,43 @@ __device__ __forceinline__ void elem_copy(const uint8_t* src, uint8_t* dst, uint
 }
 
 
+// Adds the |W - S| and |S| of one 16-byte vector to (a, b): pairwise in fp32
+// first, or each term by itself in fp64 (WIDE).
+template <int DT, bool WIDE>
+__device__ __forceinline__ void add_terms(const u32x4 w, const u32x4 s, double& a, double& b) {
+  if constexpr (!WIDE) {
+    float da, db;
+    vec_terms<DT>(w, s, da, db);
+    a += static_cast<double>(da);
+    b += static_cast<double>(db);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (DT == 1) {
+        const float s0 = bf_lo(s[k]), s1 = bf_hi(s[k]);
+        a += static_cast<double>(fabsf(bf_lo(w[k]) - s0));
+        b += static_cast<double>(fabsf(s0));
+        a += static_cast<double>(fabsf(bf_hi(w[k]) - s1));
+        b += static_cast<double>(fabsf(s1));
+      } else {
+        const float sf = __uint_as_float(s[k]);
+        a += static_cast<double>(fabsf(__uint_as_float(w[k]) - sf));
+        b += static_cast<double>(fabsf(sf));
+      }
+    }
+  }
+}
+
 // ---- score: one chunk per block and iteration ---------------------------------
-// Streams W and S of one chunk once; writes (sum|W-S|, sum|S|) in fp64.  In
-// ACCUM mode the same pass stores W into S (the next step's W(t-1)).
-template <int DT, bool ACCUM>
-__device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
+// The tile of one chunk: n elements from wb and sb on, sb on a 128-byte line
+// (wb too, or 16-byte aligned, unless ANYW).  A full tile goes through buffer
+// resources with every load of a round in flight before the first sum.  HBM
+// bounds all three forms: on a 160 M element bf16 segment (ACCUM / SNAPSHOT)
+// aligned arrays take 160 / 101 us, arrays alike at an odd element 159 / 101
+// us (element by element they took 433 / 309) and weights at an odd element
+// against the shadow 166 / 117 us (430 / 312): the loads that straddle lines.
+template <int DT, bool ACCUM, bool WIDE, bool ANYW>
+__device__ __forceinline__ void score_tile(const uint8_t* wb, uint8_t* sb, uint32_t n, double& a, double& b) {
   constexpr uint32_t ESZ = DT == 1 ? 2 : 4;
   constexpr uint32_t CE = kChunkBytes / ESZ;  // elements per chunk
   constexpr uint32_t EPV = 16 / ESZ;          // elements per 16-B vector
@@ -78,61 +110,68 @@ __device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
   constexpr uint32_t U = VPT < 4 ? VPT : 4;   // vectors per thread per round
   static_assert(VPT % U == 0, "tiling");
   const uint32_t tid = threadIdx.x;
-  const ScoreSeg sg = t.segs[t.chunk_seg[c]];
-  const uint64_t e0 = static_cast<uint64_t>(c - sg.chunk_begin) * CE;
-  const uint64_t rem = sg.numel - e0;
-  const uint32_t n = rem < CE ? static_cast<uint32_t>(rem) : CE;
-  const uint8_t* wb = reinterpret_cast<const uint8_t*>(sg.w) + e0 * ESZ;
-  uint8_t* sbp = reinterpret_cast<uint8_t*>(sg.s) + e0 * ESZ;
-
-  double a = 0.0, b = 0.0;
-  uint32_t scalar_from = 0;
-  if (sg.vec_ok) {
-    if (n == CE) {
-      const tile_t tw = make_tile(wb, kChunkBytes), ts = make_tile(sbp, kChunkBytes);
+  if (n == CE) {
+    const tile_t tw = make_tile(wb, kChunkBytes), ts = make_tile(sb, kChunkBytes);
 #pragma unroll
-      for (uint32_t r = 0; r < VPT / U; ++r) {
-        u32x4 w[U], s[U];
+    for (uint32_t r = 0; r < VPT / U; ++r) {
+      u32x4 w[U], s[U];
 #pragma unroll
-        for (uint32_t k = 0; k < U; ++k) {
-          const uint32_t off = (tid + (r * U + k) * kScoreThreads) * 16u;
-          w[k] = ld_tile(tw, off);
-          s[k] = ld_tile(ts, off);
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k) {
-          float da, db;
-          vec_terms<DT>(w[k], s[k], da, db);
-          a += static_cast<double>(da);
-          b += static_cast<double>(db);
-          if constexpr (ACCUM) st_tile(ts, (tid + (r * U + k) * kScoreThreads) * 16u, w[k]);
-        }
+      for (uint32_t k = 0; k < U; ++k) {
+        const uint32_t off = (tid + (r * U + k) * kScoreThreads) * 16u;
+        if constexpr (ANYW) w[k] = ld_any<ESZ>(wb + off);
+        else w[k] = ld_tile(tw, off);
+        s[k] = ld_tile(ts, off);
       }
-      scalar_from = n;
-    } else {
-      const u32x4* wv = reinterpret_cast<const u32x4*>(wb);
-      u32x4* sv = reinterpret_cast<u32x4*>(sbp);
-      const uint32_t nv = n / EPV;
-      for (uint32_t i = tid; i < nv; i += kScoreThreads) {
-        const u32x4 w = ld_nt(wv + i);
-        const u32x4 s = ld_nt(sv + i);
-        float da, db;
-        vec_terms<DT>(w, s, da, db);
-        a += static_cast<double>(da);
-        b += static_cast<double>(db);
-        if constexpr (ACCUM) st_nt(sv + i, w);
+#pragma unroll
+      for (uint32_t k = 0; k < U; ++k) {
+        add_terms<DT, WIDE>(w[k], s[k], a, b);
+        if constexpr (ACCUM) st_tile(ts, (tid + (r * U + k) * kScoreThreads) * 16u, w[k]);
       }
-      scalar_from = nv * EPV;
     }
+    return;
   }
-  for (uint32_t i = scalar_from + tid; i < n; i += kScoreThreads) {
-    const float wf = elem_value<DT>(wb, i), sf = elem_value<DT>(sbp, i);
+  u32x4* sv = reinterpret_cast<u32x4*>(sb);
+  const uint32_t nv = n / EPV;
+  for (uint32_t i = tid; i < nv; i += kScoreThreads) {
+    const u32x4 w = ANYW ? ld_any<ESZ>(wb + i * 16u) : ld_nt(reinterpret_cast<const u32x4*>(wb) + i);
+    const u32x4 s = ld_nt(sv + i);
+    add_terms<DT, WIDE>(w, s, a, b);
+    if constexpr (ACCUM) st_nt(sv + i, w);
+  }
+  for (uint32_t i = nv * EPV + tid; i < n; i += kScoreThreads) {
+    const float wf = elem_value<DT>(wb, i), sf = elem_value<DT>(sb, i);
     a += static_cast<double>(fabsf(wf - sf));
     b += static_cast<double>(fabsf(sf));
-    if constexpr (ACCUM) elem_copy<DT>(wb, sbp, i);
+    if constexpr (ACCUM) elem_copy<DT>(wb, sb, i);
+  }
+}
+
+// Streams W and S of one chunk once; writes (sum|W-S|, sum|S|) in fp64.  In
+// ACCUM mode the same pass stores W into S (the next step's W(t-1)).
+template <int DT, bool ACCUM>
+__device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
+  constexpr uint32_t ESZ = DT == 1 ? 2 : 4;
+  constexpr uint32_t CE = kChunkBytes / ESZ;  // elements per chunk
+  const ScoreSeg sg = t.segs[t.chunk_seg[c]];
+  const uint32_t k = c - sg.chunk_begin;
+  const uint64_t e0 = static_cast<uint64_t>(k) * CE + sg.head;  // the chunk's tile
+  const uint64_t rem = sg.numel > e0 ? sg.numel - e0 : 0;
+  const uint32_t n = rem < CE ? static_cast<uint32_t>(rem) : CE;
+  const uint8_t* w = reinterpret_cast<const uint8_t*>(sg.w);
+  uint8_t* s = reinterpret_cast<uint8_t*>(sg.s);
+
+  double a = 0.0, b = 0.0;
+  if (sg.form == kScorePairs) score_tile<DT, ACCUM, false, false>(w + e0 * ESZ, s + e0 * ESZ, n, a, b);
+  else if (sg.form == kScoreWide) score_tile<DT, ACCUM, true, false>(w + e0 * ESZ, s + e0 * ESZ, n, a, b);
+  else score_tile<DT, ACCUM, true, true>(w + e0 * ESZ, s + e0 * ESZ, n, a, b);
+  if (k == 0 && threadIdx.x < sg.head && threadIdx.x < sg.numel) {  // the elements before the first tile
+    const float wf = elem_value<DT>(w, threadIdx.x), sf = elem_value<DT>(s, threadIdx.x);
+    a += static_cast<double>(fabsf(wf - sf));
+    b += static_cast<double>(fabsf(sf));
+    if constexpr (ACCUM) elem_copy<DT>(w, s, threadIdx.x);
   }
   block_sum2<kScoreThreads>(a, b);
-  if (tid == 0) t.partials[c] = make_double2(a, b);
+  if (threadIdx.x == 0) t.partials[c] = make_double2(a, b);
 }
 
 // One chunk per block: the chunk's tables are read before any store, so they

@@ -204,14 +204,9 @@ extern "C" lc_status lc_score_layers_static(const lc_segment* segments, uint32_t
     uint32_t c = 0;
     for (uint32_t i = b.s0; i < b.s1; ++i) {
       const lc_segment& s = segments[i];
-      ScoreSeg ss;
-      ss.w = reinterpret_cast<uint64_t>(s.weight);
-      ss.s = reinterpret_cast<uint64_t>(s.shadow);
-      ss.numel = s.numel;
-      ss.chunk_begin = c;
-      ss.vec_ok = (ss.w % 16 == 0 && ss.s % 16 == 0) ? 1u : 0u;
+      b.segs.push_back(
+          score_seg(reinterpret_cast<uint64_t>(s.weight), reinterpret_cast<uint64_t>(s.shadow), s.numel, esz, c));
       c += static_cast<uint32_t>((s.numel + ce - 1) / ce);
-      b.segs.push_back(ss);
     }
     b.lcb.assign(1, 0);
     for (uint32_t l = b.l0; l < b.l1; ++l) {

@@ -130,12 +130,8 @@ lc_status build_layout(const lc_layout_desc* d, HostLayout& L) {
   uint64_t nchunks = 0;
   for (uint32_t i = 0; i < d->n_segments; ++i) {
     const lc_segment& s = L.segs[i];
-    ScoreSeg ss;
-    ss.w = reinterpret_cast<uint64_t>(s.weight);
-    ss.s = reinterpret_cast<uint64_t>(s.shadow);
-    ss.numel = s.numel;
-    ss.chunk_begin = static_cast<uint32_t>(nchunks);
-    ss.vec_ok = (ss.w % 16 == 0 && ss.s % 16 == 0) ? 1u : 0u;
+    const ScoreSeg ss = score_seg(reinterpret_cast<uint64_t>(s.weight), reinterpret_cast<uint64_t>(s.shadow), s.numel,
+                                  L.esz, static_cast<uint32_t>(nchunks));
     const uint64_t k = (s.numel + ce - 1) / ce;
     if (nchunks + k > 0xFFFFFFF0ull) return fail(LC_ERR_INVALID_ARG, "too many chunks");
     for (uint64_t j = 0; j < k; ++j) L.chunk_seg.push_back(i);
@@ -148,7 +144,14 @@ lc_status build_layout(const lc_layout_desc* d, HostLayout& L) {
     os.v = reinterpret_cast<uint64_t>(s.exp_avg_sq);
     os.numel = s.numel;
     os.chunk_begin = ss.chunk_begin;
-    os.vec_ok = (os.w % (4 * L.esz) == 0 && os.master % 16 == 0 && os.m % 16 == 0 && os.v % 16 == 0) ? 1u : 0u;
+    // the fp32 arrays hold most of what a step stores
+    os.head = os.master ? seg_head(os.master, 4) : os.m ? seg_head(os.m, 4) : seg_head(os.w, L.esz);
+    auto grouped = [&](uint64_t at) {  // whether every array is aligned to groups of four elements at element `at`
+      bool ok = (os.w + at * L.esz) % (4 * L.esz) == 0;
+      for (uint64_t a : {os.master, os.m, os.v}) ok = ok && (a == 0 || (a + at * 4) % 16 == 0);
+      return ok;
+    };
+    os.form = grouped(0) ? kOptPairs : grouped(os.head) ? kOptWide : kOptAny;
     L.opt_segs.push_back(os);
     L.layer_chunk_begin[s.layer + 1] = static_cast<uint32_t>(nchunks);
   }

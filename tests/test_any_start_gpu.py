@@ -1,0 +1,163 @@
+"""GPU: segments that start at any element, as the pieces of a ZeRO-3 rank
+do, with every array of a segment at an element offset of its own against a
+128-byte line (the weights, the shadow, the fp32 arrays and the gradient may
+all differ), and lengths around a head, a tile and the first chunk's edge.
+Every array lies between guard bytes, which stay as they were.  Scores to
+1e-5 (fp64 sums), everything else exact, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from oracle import layercheck_oracle as O
+from paper_2609_27193_amd import layercheck as LC
+from tests.conftest import gpu_available
+from tests.gpu_harness import rel_ok
+
+pytestmark = pytest.mark.gpu
+GUARD = 512  # bytes on each side of an array
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not gpu_available():
+        pytest.skip("needs an MI355X")
+    LC.load_library()
+
+
+class Arr:
+    """One array of one segment at byte ``off`` past a 128-byte line, with its host copy."""
+
+    def __init__(self, host, off):
+        import torch
+        self.host, self.off = host, GUARD + off
+        self.buf = torch.full((2 * GUARD + host.nbytes + 128,), 0xA5, dtype=torch.uint8, device="cuda")
+        assert self.buf.data_ptr() % 128 == 0
+        self.ptr = self.buf.data_ptr() + self.off
+        self.put()
+
+    def put(self):
+        import torch
+        b = torch.from_numpy(self.host.view(np.uint8).copy())
+        self.buf[self.off:self.off + b.numel()].copy_(b)
+
+    def check(self, what):
+        g = self.buf.cpu().numpy()
+        n = self.host.nbytes
+        assert np.array_equal(g[self.off:self.off + n], self.host.view(np.uint8)), what
+        assert (g[:self.off] == 0xA5).all() and (g[self.off + n:] == 0xA5).all(), f"{what}: guard bytes written"
+
+
+def bf16(x):
+    """Round-to-nearest-even bf16 bits of finite fp32 values."""
+    u = x.astype(np.float32).view(np.uint32)
+    return ((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+
+
+def lengths(esz):
+    tile, line = LC.lc_query_build()["chunk_bytes"] // esz, 128 // esz
+    return [1, line - 1, line, line + 1, tile - 1, tile, tile + 1, tile + line - 1, tile + line, 2 * tile, 2 * tile + 5,
+            3 * tile + line - 1]
+
+
+# element offsets of (weights, shadow, fp32 arrays, gradient), taken in turn by the segments
+ALIKE = [(e, e, e, e) for e in (1, 7, 8, 33, 0)]
+APART = [(1, 0, 0, 2), (0, 1, 3, 1), (5, 2, 1, 0), (0, 0, 1, 3), (8, 16, 4, 8), (3, 3, 0, 3), (0, 8, 0, 0)]
+
+
+@pytest.mark.parametrize("offsets", [ALIKE, APART], ids=["alike", "apart"])
+@pytest.mark.parametrize("dtype,master,op", [("bf16", True, "accum"), ("bf16", False, "snapshot"), ("f32", False, "accum"),
+                                             ("f32", True, "snapshot"), ("bf16", True, "adamw"), ("bf16", False, "adamw"),
+                                             ("f32", False, "adamw"), ("bf16", True, "sgd"), ("f32", False, "sgd")])
+def test_segments_at_any_element(dtype, master, op, offsets):
+    import torch
+    rng = np.random.default_rng(17)
+    esz = 2 if dtype == "bf16" else 4
+    wbits = bf16 if dtype == "bf16" else (lambda x: x.astype(np.float32))
+    draw = lambda n, s: (rng.standard_normal(n) * s).astype(np.float32)  # noqa: E731
+    sizes = lengths(esz)
+    layer_of = [i // 3 for i in range(len(sizes))]
+    N = layer_of[-1] + 1
+    segs, grad_dt = [], "f32" if master else "bf16"
+    for i, n in enumerate(sizes):
+        ow, os_, of, og = offsets[i % len(offsets)]
+        p = draw(n, 0.02)
+        d = {"w": Arr(wbits(p), ow * esz), "s": Arr(np.zeros(n, wbits(p).dtype), os_ * esz),
+             "M": Arr(p.copy(), of * 4) if master else None, "m": Arr(draw(n, 1e-3), of * 4),
+             "v": Arr(np.abs(draw(n, 1e-6)), of * 4)}
+        g = draw(n, 1.0)
+        d["g"] = Arr(g if grad_dt == "f32" else bf16(g), og * (4 if grad_dt == "f32" else 2))
+        segs.append(d)
+    arrays = ["w", "s", "m", "v"] + ["M"] * master
+    osegs = [O.OSegment(l, d["w"].host, d["s"].host, d["M"].host if master else None, d["m"].host, d["v"].host)
+             for l, d in zip(layer_of, segs)]
+    lsegs = [LC.Segment(l, n, d["w"].ptr, d["s"].ptr, d["M"].ptr if master else None, d["m"].ptr, d["v"].ptr)
+             for l, n, d in zip(layer_of, sizes, segs)]
+    mode = LC.LC_MODE_SNAPSHOT if op == "snapshot" else LC.LC_MODE_ACCUM
+    lc_dt = LC.LC_DT_BF16 if esz == 2 else LC.LC_DT_F32
+    k0 = [0.0 if l % 2 else 1e300 for l in range(N)]  # every second layer at each step, the others by age
+    orc = O.LayerCheckOracle(osegs, N, lc_dt, master, mode, k0, 2, eps_w=1e-8, t_base=0)
+    stream = torch.cuda.current_stream().cuda_stream
+    ctx = LC.lc_init_layout(LC.LayoutDesc(lsegs, N, lc_dt, master, mode, k0, 2, eps_w=1e-8, stream=stream))
+    decay = [i % 2 for i in range(len(sizes))]
+
+    def check(what):
+        torch.cuda.synchronize()
+        for i, d in enumerate(segs):
+            for a in arrays:
+                d[a].check(f"{what}: {a} of segment {i} ({sizes[i]} elements, offsets {offsets[i % len(offsets)]})")
+
+    def pack():
+        total = sum(LC.lc_record_bytes(ctx, l) for l in range(N))
+        staging = torch.full((total,), 0x5A, dtype=torch.uint8, device="cuda")
+        got = LC.lc_pack_selected(ctx, staging.data_ptr(), total, 0)
+        want, res = orc.pack(0, total)
+        assert got == res
+        h = staging.cpu().numpy()
+        k = got["bytes_written"]
+        assert np.array_equal(h[:k], want) and (h[k:] == 0x5A).all()
+        return staging, k
+
+    try:
+        check("init")
+        versions, host = [], []
+        b, k = pack()
+        versions.append({"step": 0, "mask": np.ones(N, np.uint8), "payload": b.data_ptr(), "payload_bytes": k, "keep": b})
+        host.append({"step": 0, "mask": np.ones(N, np.uint8), "payload": b.cpu().numpy()[:k]})
+        for t in (1, 2):
+            if op in ("adamw", "sgd"):
+                gdt = LC.LC_DT_F32 if grad_dt == "f32" else LC.LC_DT_BF16
+                ptrs = [d["g"].ptr for d in segs]
+                gf = [d["g"].host if grad_dt == "f32" else (d["g"].host.astype(np.uint32) << 16).view(np.float32)
+                      for d in segs]
+                if op == "adamw":
+                    LC.lc_adamw_step_score(ctx, t, ptrs, gdt, 1e-3, 0.9, 0.95, 1e-8, 0.1, t, decay)
+                    orc.adamw_step_score(t, gf, 1e-3, 0.9, 0.95, 1e-8, 0.1, t, decay)
+                else:
+                    LC.lc_sgd_step_score(ctx, t, ptrs, gdt, 1e-3, 0.1, decay)
+                    orc.sgd_step_score(t, gf, 1e-3, 0.1, decay)
+            else:
+                for d in segs:
+                    x = d["M"].host if master else (d["w"].host if esz == 4 else
+                                                    (d["w"].host.astype(np.uint32) << 16).view(np.float32))
+                    x = (x + draw(len(x), 1e-3)).astype(np.float32)
+                    d["w"].host[...] = wbits(x)
+                    d["w"].put()
+                    if master:
+                        d["M"].host[...] = x
+                        d["M"].put()
+                LC.lc_score_layers(ctx, t)
+                orc.score(t)
+            u, delta, _ = LC.lc_read_state(ctx, N)
+            assert rel_ok(u, orc.u) and rel_ok(delta, orc.delta), (u, orc.u)
+            check(f"step {t}")
+            mask, _ = LC.lc_select(ctx, t, 1.0, N)
+            orc.select(t, 1.0)
+            assert np.array_equal(mask, orc.mask)
+            b, k = pack()
+            check(f"pack {t}")
+            versions.append({"step": t, "mask": mask, "payload": b.data_ptr(), "payload_bytes": k, "keep": b})
+            host.append({"step": t, "mask": mask, "payload": b.cpu().numpy()[:k]})
+        chosen = LC.lc_restore_composite(ctx, versions, 1, N)
+        assert chosen.tolist() == orc.restore(host, 1).tolist()
+        check("restore")
+    finally:
+        LC.lc_destroy(ctx)
