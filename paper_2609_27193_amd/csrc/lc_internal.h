@@ -19,8 +19,8 @@ namespace lc {
 #ifndef LC_XCD_REMAP
 #define LC_XCD_REMAP 1
 #endif
-#ifndef LC_XCD_RUN
-#define LC_XCD_RUN 0  // 0: each XCD takes one contiguous eighth; g > 0: interleaved runs of g items
+#ifndef LC_COPY_XCD_RUN
+#define LC_COPY_XCD_RUN 64  // consecutive pieces per XCD in the pack and unpack kernels
 #endif
 #ifndef LC_MAX_GRID_BLOCKS
 #define LC_MAX_GRID_BLOCKS 0  // 0: only the dispatch limit caps a grid (testing builds set it low)
@@ -123,7 +123,7 @@ struct CopyUnit {
   uint64_t rec_off;  // byte offset of the block inside the record (256-B aligned)
   uint64_t bytes;    // payload bytes (the block is padded to kRecordAlign)
   uint32_t piece0;   // first layer-local piece index of this unit
-  uint32_t vec_ok;   // arr (and shadow) 16-B aligned
+  uint32_t head;     // bytes of arr before its first 128-byte line (at most `bytes`)
   uint32_t elem;     // element size in bytes (2 or 4)
   uint32_t pad;
 };

@@ -296,36 +296,58 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const DeviceTabl
 }
 
 // ---- byte movement of one piece ----------------------------------------------
-// len is a multiple of 2; src/dst are at least 2-byte aligned; `vec` means
-// src, dst and dst2 are 16-byte aligned.
-__device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
-                                           uint8_t* __restrict__ dst2, uint32_t len, bool vec) {
+// len bytes, a multiple of 2, from src to dst and, if given, to dst2, all at
+// least 2-byte aligned.  Full pieces go through buffer resources, the tails
+// and whatever is not 16-byte aligned through global pointers.  The callers
+// cut the pieces so that dst starts on a line (see below); src and dst2 may
+// start anywhere: on a 160 M element layer with every array at an odd element
+// the pack takes 689 us (aligned 679; two bytes a lane took 891), with the
+// shadow refreshed 763 (726; 1415) and the restore 767 (767; 1454).
+template <bool ANYS, bool ANYD>
+__device__ __forceinline__ void copy_full_piece(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
+                                                uint8_t* __restrict__ dst2) {
+  constexpr uint32_t V = kPieceBytes / 16 / kCopyThreads;
   const uint32_t tid = threadIdx.x;
+  const tile_t td = make_tile(dst, kPieceBytes);
+  u32x4 v[V];
+  if constexpr (ANYS) {
+#pragma unroll
+    for (uint32_t k = 0; k < V; ++k) v[k] = ld_any<2>(src + (tid + k * kCopyThreads) * 16u);
+  } else {
+    const tile_t ts = make_tile(src, kPieceBytes);
+#pragma unroll
+    for (uint32_t k = 0; k < V; ++k) v[k] = ld_tile(ts, (tid + k * kCopyThreads) * 16u);
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < V; ++k) st_tile(td, (tid + k * kCopyThreads) * 16u, v[k]);
+  if (dst2) {
+    const tile_t te = make_tile(dst2, kPieceBytes);
+#pragma unroll
+    for (uint32_t k = 0; k < V; ++k) {
+      const uint32_t off = (tid + k * kCopyThreads) * 16u;
+      if constexpr (ANYD) st_any(dst2 + off, v[k]);
+      else st_tile(te, off, v[k]);
+    }
+  }
+}
+
+__device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
+                                           uint8_t* __restrict__ dst2, uint32_t len) {
+  const uint32_t tid = threadIdx.x;
+  const bool any_s = reinterpret_cast<uint64_t>(src) % 16 != 0, any_d = reinterpret_cast<uint64_t>(dst2) % 16 != 0;
   uint32_t done = 0;
-  if (vec) {
+  if (reinterpret_cast<uint64_t>(dst) % 16 == 0) {
     if (len == kPieceBytes) {
-      constexpr uint32_t V = kPieceBytes / 16 / kCopyThreads;
-      const tile_t ts = make_tile(src, kPieceBytes), td = make_tile(dst, kPieceBytes);
-      u32x4 v[V];
-#pragma unroll
-      for (uint32_t k = 0; k < V; ++k) v[k] = ld_tile(ts, (tid + k * kCopyThreads) * 16u);
-#pragma unroll
-      for (uint32_t k = 0; k < V; ++k) st_tile(td, (tid + k * kCopyThreads) * 16u, v[k]);
-      if (dst2) {
-        const tile_t te = make_tile(dst2, kPieceBytes);
-#pragma unroll
-        for (uint32_t k = 0; k < V; ++k) st_tile(te, (tid + k * kCopyThreads) * 16u, v[k]);
-      }
+      if (!any_s && !any_d) copy_full_piece<false, false>(src, dst, dst2);
+      else if (!any_d) copy_full_piece<true, false>(src, dst, dst2);
+      else copy_full_piece<true, true>(src, dst, dst2);
       return;
     }
-    const u32x4* s4 = reinterpret_cast<const u32x4*>(src);
-    u32x4* d4 = reinterpret_cast<u32x4*>(dst);
-    u32x4* e4 = reinterpret_cast<u32x4*>(dst2);
     const uint32_t nv = len / 16;
     for (uint32_t i = tid; i < nv; i += kCopyThreads) {
-      const u32x4 x = ld_nt(s4 + i);
-      st_nt(d4 + i, x);
-      if (dst2) st_nt(e4 + i, x);
+      const u32x4 x = ld_any<2>(src + i * 16u);
+      st_nt(reinterpret_cast<u32x4*>(dst) + i, x);
+      if (dst2) st_any(dst2 + i * 16u, x);
     }
     done = nv * 16;
   }
@@ -338,8 +360,6 @@ __device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint
     if (dst2) f2[i] = x;
   }
 }
-
-
 
 // ---- pack: selected records into the staging buffer ---------------------------
 // Work item q is piece q (relative to piece_base) of the selected records of
@@ -362,7 +382,7 @@ __device__ __forceinline__ void pack_piece(const DeviceTables& t, uint32_t first
   uint8_t* dst = staging + (t.sel_rec_prefix[lo] - rec_base) + u.rec_off + off;
   const uint8_t* src = reinterpret_cast<const uint8_t*>(u.arr) + off;
   uint8_t* dst2 = (REFRESH && u.shadow) ? reinterpret_cast<uint8_t*>(u.shadow) + off : nullptr;
-  copy_piece(src, dst, dst2, len, u.vec_ok != 0);
+  copy_piece(src, dst, dst2, len);
   if (off + len == u.bytes) {  // zero the block's padding
     const uint32_t pad = static_cast<uint32_t>(round_up(u.bytes, kRecordAlign) - u.bytes);
     uint16_t* z = reinterpret_cast<uint16_t*>(dst + len);
@@ -376,12 +396,14 @@ template <bool REFRESH>
 __global__ __launch_bounds__(kCopyThreads) void pack_kernel(const DeviceTables t, uint32_t first,
                                                             uint32_t last, uint64_t piece_base,
                                                             uint64_t rec_base, uint8_t* staging) {
-  pack_piece<REFRESH>(t, first, last, piece_base + remap_xcd(blockIdx.x, gridDim.x), rec_base, staging);
+  pack_piece<REFRESH>(t, first, last, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, gridDim.x), rec_base, staging);
 }
 
 // ---- unpack: composite restore from device-resident records --------------------
 // rank r restores layer rank_layer[r] from the record at address rank_src[r];
-// every W block also refreshes the shadow.
+// every W block also refreshes the shadow.  An array's pieces start behind its
+// head, on a line of the array, so that the stores do not split lines; the
+// array's first piece takes the head with it, and the last may be empty.
 __device__ __forceinline__ void unpack_piece(const DeviceTables& t, uint32_t n_ranks, uint64_t q) {
   uint32_t lo = 0, hi = n_ranks;
   while (hi - lo > 1) {
@@ -391,20 +413,21 @@ __device__ __forceinline__ void unpack_piece(const DeviceTables& t, uint32_t n_r
   const uint32_t l = t.rank_layer[lo];
   const uint64_t lp = q - t.rank_piece_prefix[lo];
   const CopyUnit u = t.units[t.piece_unit[t.layer_piece_begin[l] + lp]];
-  const uint64_t off = (lp - u.piece0) * kPieceBytes;
-  const uint64_t rem = u.bytes - off;
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(t.rank_src[lo]) + u.rec_off;
+  uint8_t* dst = reinterpret_cast<uint8_t*>(u.arr);
+  uint8_t* dst2 = u.shadow ? reinterpret_cast<uint8_t*>(u.shadow) : nullptr;
+  const uint32_t p = static_cast<uint32_t>(lp) - u.piece0;
+  if (p == 0 && u.head) copy_piece(src, dst, dst2, u.head);
+  const uint64_t off = static_cast<uint64_t>(p) * kPieceBytes + u.head;
+  const uint64_t rem = u.bytes > off ? u.bytes - off : 0;
   const uint32_t len = rem < kPieceBytes ? static_cast<uint32_t>(rem) : kPieceBytes;
-  const uint64_t rec = t.rank_src[lo];
-  const uint8_t* src = reinterpret_cast<const uint8_t*>(rec) + u.rec_off + off;
-  uint8_t* dst = reinterpret_cast<uint8_t*>(u.arr) + off;
-  uint8_t* dst2 = u.shadow ? reinterpret_cast<uint8_t*>(u.shadow) + off : nullptr;
-  copy_piece(src, dst, dst2, len, u.vec_ok != 0 && (rec & 15) == 0);
+  if (len) copy_piece(src + off, dst + off, dst2 ? dst2 + off : nullptr, len);
 }
 
 // One piece per block, from piece_base on (split like the pack).
 __global__ __launch_bounds__(kCopyThreads) void unpack_kernel(const DeviceTables t, uint32_t n_ranks,
                                                               uint64_t piece_base) {
-  unpack_piece(t, n_ranks, piece_base + remap_xcd(blockIdx.x, gridDim.x));
+  unpack_piece(t, n_ranks, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, gridDim.x));
 }
 
 // Each launch takes the largest grid one dispatch allows (grid_for) and the

@@ -176,7 +176,7 @@ lc_status build_layout(const lc_layout_desc* d, HostLayout& L) {
         u.bytes = s.numel * u.elem;
         u.rec_off = rec;
         u.piece0 = static_cast<uint32_t>(pieces);
-        u.vec_ok = (u.arr % 16 == 0 && u.shadow % 16 == 0) ? 1u : 0u;
+        u.head = static_cast<uint32_t>(std::min<uint64_t>((kLineBytes - u.arr % kLineBytes) % kLineBytes, u.bytes));
         const uint64_t k = (u.bytes + kPieceBytes - 1) / kPieceBytes;
         const uint32_t uid = static_cast<uint32_t>(L.units.size());
         for (uint64_t j = 0; j < k; ++j) L.piece_unit.push_back(uid);
