@@ -38,7 +38,7 @@ static_assert(kChunkBytes % (16u * kScoreThreads) == 0, "score tiling: whole vec
 static_assert(kPieceBytes % (16u * kCopyThreads) == 0, "pack tiling");
 constexpr uint32_t kRecordAlign = 256u;
 constexpr uint32_t kFinalizeThreads = 1024;
-constexpr uint32_t kSelectThreads = 256;
+constexpr uint32_t kSelectThreads = 256;  // beyond 64 layers
 
 // Resident blocks per CU of the streaming kernels (0: as many as registers
 // and waves allow), held there by a dynamic LDS reservation the kernel never
@@ -165,10 +165,10 @@ struct SgdScalars {
   float lr, decay;
 };
 
-// Written by the select kernel to device memory and to a pinned host mirror,
-// followed by the 0/1 mask of n_layers bytes.  In the mirror `seq` is written
-// last, after a system-scope fence: the host waits for the number it passed
-// to the kernel instead of synchronising the stream.
+// Written by the select kernel to pinned host memory, followed by the 0/1 mask
+// of n_layers bytes.  `seq` is written last, after system-scope fences: the
+// host waits for the number it passed to the kernel instead of synchronising
+// the stream.
 struct SelectHeader {
   uint32_t n_selected;
   uint32_t n_forced;
@@ -208,8 +208,7 @@ struct DeviceTables {
   uint32_t* sel_layer;                // [N] layer of each selected rank
   uint64_t* sel_rec_prefix;           // [N+1] record byte offsets by rank
   uint64_t* sel_piece_prefix;         // [N+1] piece offsets by rank
-  SelectHeader* result;               // header + mask[N]
-  SelectHeader* host_result;          // pinned host mirror of result (device address)
+  SelectHeader* host_result;          // pinned host memory (device address): header + mask[N]
   const OptSeg* opt_segs;             // [n_segments]
   const GradSeg* grad_segs;           // [n_segments], refreshed per optimizer call
   // restore scratch

@@ -523,7 +523,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   ScoreSeg* segs; uint32_t* chunk_seg; uint32_t* lcb; double2* partials; double* u; double* delta;
   int64_t* t_last; double* k0; uint64_t* numel; uint64_t* rec; uint64_t* lpieces; CopyUnit* units;
   uint32_t* piece_unit; uint64_t* lpb; uint32_t* sel_layer; uint64_t* srp; uint64_t* spp;
-  SelectHeader* result; uint32_t* rank_layer; uint64_t* rank_src; uint64_t* rpp;
+  uint32_t* rank_layer; uint64_t* rank_src; uint64_t* rpp;
   LC_TRY(dev_alloc(c, &segs, L.score_segs.size()));
   LC_TRY(dev_alloc(c, &chunk_seg, L.chunk_seg.size()));
   LC_TRY(dev_alloc(c, &lcb, N + 1));
@@ -541,11 +541,6 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   LC_TRY(dev_alloc(c, &sel_layer, N));
   LC_TRY(dev_alloc(c, &srp, N + 1));
   LC_TRY(dev_alloc(c, &spp, N + 1));
-  {
-    uint8_t* r8;
-    LC_TRY(dev_alloc(c, &r8, sizeof(SelectHeader) + N));
-    result = reinterpret_cast<SelectHeader*>(r8);
-  }
   OptSeg* opt_segs;
   LC_TRY(dev_alloc(c, &opt_segs, L.opt_segs.size()));
   LC_TRY(dev_alloc(c, &c->d_grad, L.opt_segs.size()));
@@ -583,7 +578,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   t.segs = segs; t.chunk_seg = chunk_seg; t.layer_chunk_begin = lcb; t.partials = partials;
   t.u = u; t.delta = delta; t.t_last = t_last; t.k0 = k0; t.numel = numel; t.rec_bytes = rec;
   t.layer_pieces = lpieces; t.units = units; t.piece_unit = piece_unit; t.layer_piece_begin = lpb;
-  t.sel_layer = sel_layer; t.sel_rec_prefix = srp; t.sel_piece_prefix = spp; t.result = result;
+  t.sel_layer = sel_layer; t.sel_rec_prefix = srp; t.sel_piece_prefix = spp;
   t.rank_layer = rank_layer; t.rank_src = rank_src; t.rank_piece_prefix = rpp;
   t.opt_segs = opt_segs; t.grad_segs = c->d_grad;
 
