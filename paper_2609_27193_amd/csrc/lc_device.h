@@ -15,6 +15,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // through global-address-space pointers gives global_load/global_store
 // instead of flat accesses (no aperture check, no LDS-counter coupling).
 typedef __attribute__((address_space(1))) u32x4 g_u32x4;
+typedef __attribute__((address_space(1))) uint16_t g_u16;
+typedef __attribute__((address_space(1))) float g_f32;
 __device__ __forceinline__ u32x4 ld_nt(const u32x4* p) {
   return __builtin_nontemporal_load((const g_u32x4*)p);
 }
@@ -105,42 +107,55 @@ __device__ __forceinline__ uint32_t remap_xcd_runs(uint32_t x, uint32_t G) {
 }
 
 // ---- wave64 / block reductions of an fp64 pair, fixed order ------------------
-__device__ __forceinline__ double dpp_f64(double v, int ctrl_sel) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  if (ctrl_sel == 0) {  // quad_perm [1,0,3,2]: partner = lane ^ 1
-    lo = __builtin_amdgcn_update_dpp(0, lo, 0xB1, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(0, hi, 0xB1, 0xF, 0xF, false);
-  } else {              // quad_perm [2,3,0,1]: partner = lane ^ 2
-    lo = __builtin_amdgcn_update_dpp(0, lo, 0x4E, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(0, hi, 0x4E, 0xF, 0xF, false);
-  }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
   return __hiloint2double(hi, lo);
 }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void dpp_add2(double& a, double& b) {
+  a += dpp_f64<CTRL, ROWS>(a);
+  b += dpp_f64<CTRL, ROWS>(b);
+}
 
+// Sum of (a, b) over a wave; the result is valid in lane 63.  FAST stays in
+// the vector ALU (DPP moves and row broadcasts, no LDS trips), which shortens
+// a block's tail, the time its slot holds no loads in flight: with it the
+// ACCUM score runs best at 3 blocks per CU (1147 -> 1132 us on 1.2 B bf16
+// weights, 4 per CU before).  The SNAPSHOT score, which only reads, loses by
+// it (at 5 per CU 693 -> 704 us, at 4 708): more loads are in flight than HBM
+// serves well.
+template <bool FAST>
 __device__ __forceinline__ void wave_sum2(double& a, double& b) {
-  a += dpp_f64(a, 0);
-  b += dpp_f64(b, 0);
-  a += dpp_f64(a, 1);
-  b += dpp_f64(b, 1);
+  dpp_add2<0xB1, 0xF>(a, b);  // quad_perm [1,0,3,2]: lane ^ 1
+  dpp_add2<0x4E, 0xF>(a, b);  // quad_perm [2,3,0,1]: lane ^ 2
+  if constexpr (FAST) {
+    dpp_add2<0x141, 0xF>(a, b);  // row_half_mirror: the other quad of each eight
+    dpp_add2<0x140, 0xF>(a, b);  // row_mirror: the other half of each row
+    dpp_add2<0x142, 0xA>(a, b);  // row_bcast:15 into rows 1 and 3
+    dpp_add2<0x143, 0xC>(a, b);  // row_bcast:31 into rows 2 and 3
+  } else {
 #pragma unroll
-  for (int m = 4; m < 64; m <<= 1) {
-    a += __shfl_xor(a, m, 64);
-    b += __shfl_xor(b, m, 64);
+    for (int m = 4; m < 64; m <<= 1) {
+      a += __shfl_xor(a, m, 64);
+      b += __shfl_xor(b, m, 64);
+    }
   }
 }
 
-// Sum of (a, b) over a block of NT threads; the result is valid in thread 0.
-template <int NT>
+// Sum of (a, b) over a block of NT threads; the result is valid in the last.
+template <int NT, bool FAST = true>
 __device__ __forceinline__ void block_sum2(double& a, double& b) {
   __shared__ double sa[NT / 64], sb[NT / 64];
-  wave_sum2(a, b);
+  wave_sum2<FAST>(a, b);
   const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
+  if ((threadIdx.x & 63) == 63) {
     sa[wave] = a;
     sb[wave] = b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == NT - 1) {
     double x = sa[0], y = sb[0];
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) {

@@ -42,32 +42,30 @@ constexpr uint32_t kSelectThreads = 256;  // beyond 64 layers
 
 // Resident blocks per CU of the streaming kernels (0: as many as registers
 // and waves allow), held there by a dynamic LDS reservation the kernel never
-// touches.  Fewer streams open at once let HBM turn between reads and writes
-// less often; kernels that only read, and kernels that end each block with a
-// reduction (its tail leaves the block's slot without loads in flight), want
-// more.  Measured on
-// MI355X, same arrays, one process (GB/s, unreserved -> reserved):
-//   ACCUM score (two reads, one write), 4 per CU: 8B 6425 -> 6688,
-//     70B shard 6230 -> 6324, 13B 6070 -> 6158, Qwen2.5-14B 6414 -> 6574;
-//     2 per CU loses 14%, 3 ties 4 on the larger states;
-//   SNAPSHOT score (two reads), 5 per CU: 8B 6960 -> 7224, 13B 7069 -> 7232,
-//     Qwen2.5-14B 6590 -> 6733, 70B shard 6990 -> 7219 (3 and 4 per CU lose);
-//   pack and unpack (copies), 6 per CU: +0.2..1.8% (3 per CU: -12%);
-//   fused AdamW, 2 per CU: 5930 -> 6004; fused SGD: no gain at 2..6.
+// touches.  HBM serves mixed reads and writes best with about 48 KB of loads
+// open per CU, and the more of them come in one block's burst the better;
+// kernels that only read want more open.  Measured on MI355X, same arrays, one
+// process (us at the blocks per CU given, 1.24 B bf16 weights; the optimizer
+// steps are in lc_optim.hip):
+//   ACCUM score (two reads, one write; 16 KB of loads a block): 2: 1292, 3:
+//     1132, 4: 1147, 5: 1163;
+//   SNAPSHOT score (two reads): 3: 829, 4: 749, 5: 693, 6: 718;
+//   pack (copies, 8 KB a block), a fifth of the layers: 4: 787, 5: 779, 6:
+//     789, 8: 807; with the shadow refreshed 846, 847, 859, 880.
+// Not kept: several chunks or pieces per block (score 1157-1360, pack 786-829),
+// blocks of one wave (score 1181-1258), and the chunk's addresses in one table
+// entry with the kernel arguments preloaded (1130-1133: the lookups are hidden).
 #ifndef LC_SCORE_ACCUM_BLOCKS_PER_CU
-#define LC_SCORE_ACCUM_BLOCKS_PER_CU 4
+#define LC_SCORE_ACCUM_BLOCKS_PER_CU 3
 #endif
 #ifndef LC_SCORE_SNAPSHOT_BLOCKS_PER_CU
 #define LC_SCORE_SNAPSHOT_BLOCKS_PER_CU 5
 #endif
 #ifndef LC_COPY_BLOCKS_PER_CU
-#define LC_COPY_BLOCKS_PER_CU 6
+#define LC_COPY_BLOCKS_PER_CU 5
 #endif
-#ifndef LC_ADAMW_BLOCKS_PER_CU
-#define LC_ADAMW_BLOCKS_PER_CU 2
-#endif
-#ifndef LC_SGD_BLOCKS_PER_CU
-#define LC_SGD_BLOCKS_PER_CU 0
+#ifndef LC_OPT_BLOCKS_PER_CU
+#define LC_OPT_BLOCKS_PER_CU 0  // 0: by the bytes a block loads (lc_optim.hip)
 #endif
 // Dynamic LDS bytes per block that leave room for at most `blocks_per_cu`
 // blocks on a CU of the current device (0 when blocks_per_cu is 0 or the

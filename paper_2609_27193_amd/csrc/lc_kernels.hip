@@ -49,18 +49,18 @@ __device__ __forceinline__ void vec_terms(const u32x4 w, const u32x4 s, float& d
 template <int DT>
 __device__ __forceinline__ float elem_value(const uint8_t* base, uint64_t i) {
   if constexpr (DT == 1) {
-    return __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(base)[i]) << 16);
+    return __uint_as_float(static_cast<uint32_t>(((const g_u16*)base)[i]) << 16);
   } else {
-    return reinterpret_cast<const float*>(base)[i];
+    return ((const g_f32*)base)[i];
   }
 }
 
 template <int DT>
 __device__ __forceinline__ void elem_copy(const uint8_t* src, uint8_t* dst, uint64_t i) {
   if constexpr (DT == 1) {
-    reinterpret_cast<uint16_t*>(dst)[i] = reinterpret_cast<const uint16_t*>(src)[i];
+    ((g_u16*)dst)[i] = ((const g_u16*)src)[i];
   } else {
-    reinterpret_cast<float*>(dst)[i] = reinterpret_cast<const float*>(src)[i];
+    ((g_f32*)dst)[i] = ((const g_f32*)src)[i];
   }
 }
 
@@ -170,8 +170,8 @@ __device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
     b += static_cast<double>(fabsf(sf));
     if constexpr (ACCUM) elem_copy<DT>(w, s, threadIdx.x);
   }
-  block_sum2<kScoreThreads>(a, b);
-  if (threadIdx.x == 0) t.partials[c] = make_double2(a, b);
+  block_sum2<kScoreThreads, ACCUM>(a, b);
+  if (threadIdx.x == kScoreThreads - 1) t.partials[c] = make_double2(a, b);
 }
 
 // One chunk per block: the chunk's tables are read before any store, so they
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const Device
   double x = (a[0] + a[1]) + (a[2] + a[3]);
   double y = (b[0] + b[1]) + (b[2] + b[3]);
   block_sum2<kFinalizeThreads>(x, y);
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == kFinalizeThreads - 1) {
     const double n = static_cast<double>(t.numel[l]);
     const double u = (x / n) / (y / n + t.eps_w);
     t.u[l] = u;

@@ -14,6 +14,14 @@ namespace {
 constexpr int kAdamW = 0;
 constexpr int kSGD = 1;
 
+// Threads per block: a block takes its whole tile in one burst of loads, so
+// 512 threads of two groups for the 4096 elements of a bf16 chunk (256 threads
+// of four: AdamW 1663 us, 512: 1529, one block per CU, 336 M parameters).  An
+// fp32 chunk has 2048 elements: 256 threads of two groups (AdamW 1465 us, 512
+// threads of one: 1475), with a master 512 (1822; 256: 1840).
+template <int WDT, bool MASTER>
+constexpr uint32_t kOptThreads = WDT == 1 || MASTER ? 512 : 256;
+
 __device__ __forceinline__ uint16_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
   if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7FC0u;  // NaN stays a quiet NaN
@@ -97,28 +105,23 @@ struct Group4 {
   __device__ __forceinline__ void set_grad(u32x4 x) {
     for (int k = 0; k < 4; ++k) g[k] = __uint_as_float(x[k]);
   }
-  __device__ __forceinline__ void load_grad(const ChunkPtrs& c, uint32_t j) {
+  __device__ __forceinline__ void load_p(const ChunkPtrs& c, uint32_t j) {
+    if constexpr (!MASTER && WDT == 1) p = widen_bf16x4(ld_any2(c.p + j * 8u));
+    else p = ld_any<4>(c.p + j * 16u);
+  }
+  __device__ __forceinline__ void load_m(const ChunkPtrs& c, uint32_t j) { m = ld_any<4>(c.m + j * 16u); }
+  __device__ __forceinline__ void load_v(const ChunkPtrs& c, uint32_t j) { v = ld_any<4>(c.v + j * 16u); }
+  __device__ __forceinline__ void load_g(const ChunkPtrs& c, uint32_t j) {
     if constexpr (GDT == 1) set_grad(ld_any2(c.g + j * 8u));
     else set_grad(ld_any<4>(c.g + j * 16u));
   }
-  __device__ __forceinline__ void load(const ChunkPtrs& c, uint32_t j) {
-    if constexpr (!MASTER && WDT == 1) p = widen_bf16x4(ld_any2(c.p + j * 8u));
-    else p = ld_any<4>(c.p + j * 16u);
-    if constexpr (OPT == kAdamW) {
-      m = ld_any<4>(c.m + j * 16u);
-      v = ld_any<4>(c.v + j * 16u);
-    }
-    load_grad(c, j);
-  }
-  __device__ __forceinline__ void load(const ChunkTiles& t, uint32_t j) {
+  __device__ __forceinline__ void load_p(const ChunkTiles& t, uint32_t j) {
     if constexpr (!MASTER && WDT == 1) p = widen_bf16x4(ld_tile2(t.p, j * 8u));
     else p = ld_tile(t.p, j * 16u);
-    if constexpr (OPT == kAdamW) {
-      m = ld_tile(t.m, j * 16u);
-      v = ld_tile(t.v, j * 16u);
-    }
   }
-  __device__ __forceinline__ void load_grad(const ChunkTiles& t, uint32_t j) {
+  __device__ __forceinline__ void load_m(const ChunkTiles& t, uint32_t j) { m = ld_tile(t.m, j * 16u); }
+  __device__ __forceinline__ void load_v(const ChunkTiles& t, uint32_t j) { v = ld_tile(t.v, j * 16u); }
+  __device__ __forceinline__ void load_g(const ChunkTiles& t, uint32_t j) {
     if constexpr (GDT == 1) set_grad(ld_tile2(t.g, j * 8u));
     else set_grad(ld_tile(t.g, j * 16u));
   }
@@ -155,25 +158,46 @@ struct Group4 {
       b += static_cast<double>((q[0] + q[1]) + (q[2] + q[3]));
     }
   }
-  __device__ __forceinline__ void store(const ChunkPtrs& c, uint32_t j) const {
-    if constexpr (OPT == kAdamW) {
-      st_any4(c.m + j * 16u, m);
-      st_any4(c.v + j * 16u, v);
-    }
-    if constexpr (MASTER) st_any4(c.p + j * 16u, p);
+  __device__ __forceinline__ void store_m(const ChunkPtrs& c, uint32_t j) const { st_any4(c.m + j * 16u, m); }
+  __device__ __forceinline__ void store_v(const ChunkPtrs& c, uint32_t j) const { st_any4(c.v + j * 16u, v); }
+  __device__ __forceinline__ void store_p(const ChunkPtrs& c, uint32_t j) const { st_any4(c.p + j * 16u, p); }
+  __device__ __forceinline__ void store_w(const ChunkPtrs& c, uint32_t j) const {
     if constexpr (WDT == 1) st_any2(c.w + j * 8u, narrow_bf16x4(p));
     else st_any4(c.w + j * 16u, p);
   }
-  __device__ __forceinline__ void store(const ChunkTiles& t, uint32_t j) const {
-    if constexpr (OPT == kAdamW) {
-      st_tile(t.m, j * 16u, m);
-      st_tile(t.v, j * 16u, v);
-    }
-    if constexpr (MASTER) st_tile(t.p, j * 16u, p);
+  __device__ __forceinline__ void store_m(const ChunkTiles& t, uint32_t j) const { st_tile(t.m, j * 16u, m); }
+  __device__ __forceinline__ void store_v(const ChunkTiles& t, uint32_t j) const { st_tile(t.v, j * 16u, v); }
+  __device__ __forceinline__ void store_p(const ChunkTiles& t, uint32_t j) const { st_tile(t.p, j * 16u, p); }
+  __device__ __forceinline__ void store_w(const ChunkTiles& t, uint32_t j) const {
     if constexpr (WDT == 1) st_tile2(t.w, j * 8u, narrow_bf16x4(p));
     else st_tile(t.w, j * 16u, p);
   }
 };
+
+// N groups of a thread, loaded, updated and stored one array after the other:
+// each array's part of the tile is one run of HBM accesses (336 M parameters,
+// one block per CU: AdamW 1529 us, group after group 1542).
+template <int OPT, int WDT, int GDT, bool MASTER, bool WIDE, uint32_t N, typename SRC, typename GSRC, typename SC>
+__device__ __forceinline__ void optim_groups(const SRC& t, const GSRC& tg, uint32_t j, const SC& sc, bool decay,
+                                             double& a, double& b) {
+  Group4<OPT, WDT, GDT, MASTER> grp[N];
+#define LC_EACH_GROUP(stmt)           \
+  _Pragma("unroll") for (uint32_t k = 0; k < N; ++k) stmt
+  LC_EACH_GROUP(grp[k].load_p(t, j + k * kOptThreads<WDT, MASTER>);)
+  if constexpr (OPT == kAdamW) {
+    LC_EACH_GROUP(grp[k].load_m(t, j + k * kOptThreads<WDT, MASTER>);)
+    LC_EACH_GROUP(grp[k].load_v(t, j + k * kOptThreads<WDT, MASTER>);)
+  }
+  LC_EACH_GROUP(grp[k].load_g(tg, j + k * kOptThreads<WDT, MASTER>);)
+  LC_EACH_GROUP(grp[k].template update<WIDE>(sc, decay, a, b);)
+  if constexpr (OPT == kAdamW) {
+    LC_EACH_GROUP(grp[k].store_m(t, j + k * kOptThreads<WDT, MASTER>);)
+    LC_EACH_GROUP(grp[k].store_v(t, j + k * kOptThreads<WDT, MASTER>);)
+  }
+  if constexpr (MASTER) LC_EACH_GROUP(grp[k].store_p(t, j + k * kOptThreads<WDT, MASTER>);)
+  LC_EACH_GROUP(grp[k].store_w(t, j + k * kOptThreads<WDT, MASTER>);)
+#undef LC_EACH_GROUP
+}
 
 // A full tile: every load in flight before the first update.  ANYG: the
 // gradient at any alignment; ANY: every array.  On a 160 M element segment
@@ -184,36 +208,23 @@ struct Group4 {
 template <int OPT, int WDT, int GDT, bool MASTER, bool WIDE, bool ANYG, bool ANY, typename SC>
 __device__ __forceinline__ void optim_tile(const ChunkPtrs& c, const SC& sc, bool decay, double& a, double& b) {
   constexpr uint32_t WSZ = WDT == 1 ? 2 : 4, GSZ = GDT == 1 ? 2 : 4;
-  constexpr uint32_t CE = kChunkBytes / WSZ;        // elements per chunk (the score chunks)
-  constexpr uint32_t GPT = CE / 4 / kScoreThreads;  // 4-element groups per thread in a full chunk
-  static_assert(GPT >= 1 && CE % (4 * kScoreThreads) == 0, "tiling");
-  const uint32_t tid = threadIdx.x;
-  ChunkTiles t;
-  t.w = make_tile(c.w, CE * WSZ);
-  t.p = MASTER ? make_tile(c.p, CE * 4) : t.w;
-  t.g = make_tile(c.g, CE * GSZ);
-  t.m = t.v = t.p;
-  if constexpr (OPT == kAdamW) {
-    t.m = make_tile(c.m, CE * 4);
-    t.v = make_tile(c.v, CE * 4);
-  }
-  Group4<OPT, WDT, GDT, MASTER> grp[GPT];
-#pragma unroll
-  for (uint32_t k = 0; k < GPT; ++k) {
-    const uint32_t j = tid + k * kScoreThreads;
-    if constexpr (ANY) {
-      grp[k].load(c, j);
-    } else {
-      grp[k].load(t, j);
-      if constexpr (ANYG) grp[k].load_grad(c, j);
-      else grp[k].load_grad(t, j);
+  constexpr uint32_t CE = kChunkBytes / WSZ;      // elements per chunk (the score chunks)
+  constexpr uint32_t GPT = CE / 4 / kOptThreads<WDT, MASTER>;  // 4-element groups per thread in a full chunk
+  static_assert(GPT >= 1 && CE % (4 * kOptThreads<WDT, MASTER>) == 0, "tiling");
+  if constexpr (ANY) {
+    optim_groups<OPT, WDT, GDT, MASTER, WIDE, GPT>(c, c, threadIdx.x, sc, decay, a, b);
+  } else {
+    ChunkTiles t;
+    t.w = make_tile(c.w, CE * WSZ);
+    t.p = MASTER ? make_tile(c.p, CE * 4) : t.w;
+    t.g = make_tile(c.g, CE * GSZ);
+    t.m = t.v = t.p;
+    if constexpr (OPT == kAdamW) {
+      t.m = make_tile(c.m, CE * 4);
+      t.v = make_tile(c.v, CE * 4);
     }
-  }
-#pragma unroll
-  for (uint32_t k = 0; k < GPT; ++k) {
-    grp[k].template update<WIDE>(sc, decay, a, b);
-    if constexpr (ANY) grp[k].store(c, tid + k * kScoreThreads);
-    else grp[k].store(t, tid + k * kScoreThreads);
+    if constexpr (ANYG) optim_groups<OPT, WDT, GDT, MASTER, WIDE, GPT>(t, c, threadIdx.x, sc, decay, a, b);
+    else optim_groups<OPT, WDT, GDT, MASTER, WIDE, GPT>(t, t, threadIdx.x, sc, decay, a, b);
   }
 }
 
@@ -271,24 +282,21 @@ __device__ __forceinline__ void optim_chunk(const DeviceTables& t, const SC& sc,
     optim_tile<OPT, WDT, GDT, MASTER, true, true, true>(cp, sc, decay, a, b);
   } else {
     const uint32_t ng = n / 4;
-    for (uint32_t i = tid; i < ng; i += kScoreThreads) {
-      Group4<OPT, WDT, GDT, MASTER> grp;
-      grp.load(cp, i);
-      if (pairs) grp.template update<false>(sc, decay, a, b);
-      else grp.template update<true>(sc, decay, a, b);
-      grp.store(cp, i);
+    for (uint32_t i = tid; i < ng; i += kOptThreads<WDT, MASTER>) {
+      if (pairs) optim_groups<OPT, WDT, GDT, MASTER, false, 1>(cp, cp, i, sc, decay, a, b);
+      else optim_groups<OPT, WDT, GDT, MASTER, true, 1>(cp, cp, i, sc, decay, a, b);
     }
-    for (uint32_t i = ng * 4 + tid; i < n; i += kScoreThreads)
+    for (uint32_t i = ng * 4 + tid; i < n; i += kOptThreads<WDT, MASTER>)
       optim_elem<OPT, WDT, GDT, MASTER>(sg, gs, sc, e0 + i, a, b);
   }
   // the elements before the first tile
   if (k == 0 && tid < sg.head && tid < sg.numel) optim_elem<OPT, WDT, GDT, MASTER>(sg, gs, sc, tid, a, b);
-  block_sum2<kScoreThreads>(a, b);
-  if (tid == 0) t.partials[c] = make_double2(a, b);
+  block_sum2<kOptThreads<WDT, MASTER>>(a, b);
+  if (tid == kOptThreads<WDT, MASTER> - 1) t.partials[c] = make_double2(a, b);
 }
 
 template <int OPT, int WDT, int GDT, bool MASTER, bool LOOP, typename SC>
-__global__ __launch_bounds__(kScoreThreads) void optim_kernel(const DeviceTables t, const SC sc) {
+__global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const DeviceTables t, const SC sc) {
   if constexpr (!LOOP) {
     optim_chunk<OPT, WDT, GDT, MASTER>(t, sc, remap_xcd(blockIdx.x, gridDim.x));
   } else {
@@ -302,14 +310,34 @@ __global__ __launch_bounds__(kScoreThreads) void optim_kernel(const DeviceTables
   }
 }
 
+// Blocks per CU of an optimizer step, by the bytes that one block loads and
+// stores.  HBM moves most with about 100 KB of them open per CU, in tiles as
+// large as fit: on 336 M parameters (us at 1 / 2 / 3 / 4 / 5 blocks per CU)
+//   AdamW, master, bf16 / fp32 gradients (112 / 120 KB): 1546 / 1656 / 1722,
+//     1682 / 1804 / 1852;
+//   AdamW, bf16 weights alone (88 / 96 KB): 1280 / 1230 / 1306, 1369 / 1363 /
+//     1434: a lone block leaves gaps that its tile does not make up for;
+//   AdamW, fp32 weights (52-64 KB): 1675 / 1478 / 1531;
+//   SGD, master (48 / 56 KB): 753 / 648 / 677 / 689, 839 / 773 / 813;
+//   SGD, bf16 weights alone, bf16 / fp32 gradients (24 / 32 KB): 646 / 437 /
+//     335 / 320 / 320, 667 / 475 / 426 / 440;
+//   SGD, fp32 weights, bf16 gradients (20 KB): 1358 / 817 / 619 / 540 / 532.
+constexpr uint32_t kOptBytesPerCU = 100 * 1024;
+
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
 void launch_optim_t(const DeviceTables& t, const SC& sc, hipStream_t st) {
-  const uint32_t g = grid_for(t.n_chunks, kScoreThreads);
-  const uint32_t lds = occupancy_lds(OPT == kAdamW ? LC_ADAMW_BLOCKS_PER_CU : LC_SGD_BLOCKS_PER_CU);
+  const uint32_t g = grid_for(t.n_chunks, kOptThreads<WDT, MASTER>);
+  constexpr uint32_t CE = kChunkBytes / (WDT == 1 ? 2 : 4);
+  constexpr uint32_t wsz = WDT == 1 ? 2 : 4;
+  constexpr uint32_t tile = CE * ((MASTER ? 8 + wsz : 2 * wsz) + (OPT == kAdamW ? 16 : 0) + (GDT == 1 ? 2 : 4));
+  constexpr uint32_t fit = (kOptBytesPerCU + tile / 2) / tile;
+  constexpr uint32_t blocks = LC_OPT_BLOCKS_PER_CU ? LC_OPT_BLOCKS_PER_CU
+                              : tile >= kOptBytesPerCU ? 1 : fit < 2 ? 2 : fit;
+  const uint32_t lds = occupancy_lds(blocks);
   if (g == t.n_chunks)
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kScoreThreads), lds, st, t, sc);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc);
   else
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kScoreThreads), lds, st, t, sc);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc);
 }
 
 template <int OPT, typename SC>
