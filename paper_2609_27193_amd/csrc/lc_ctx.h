@@ -57,6 +57,7 @@ struct lc_ctx {
   using DeviceTables = lc::DeviceTables;
   using SelectHeader = lc::SelectHeader;
   using GradSeg = lc::GradSeg;
+  using HostState = lc::HostState;
   HostLayout L;
   int mode = 0;
   int64_t s_max = 1;
@@ -67,10 +68,13 @@ struct lc_ctx {
   std::vector<void*> allocations;
   SelectHeader* h_result = nullptr;  // pinned, coherent: header + mask[N], written by the select kernel
   uint64_t result_seq = 0;           // sequence number of the last select kernel enqueued
-  GradSeg* h_grad = nullptr;         // pinned: per-call gradient table
+  HostState* h_state = nullptr;      // pinned, coherent: numbers, per-layer state, restore tables
+  HostState* dev_h_state = nullptr;  // its device address
+  uint64_t state_seq = 0;            // sequence number of the last state read enqueued
+  GradSeg* h_grad = nullptr;         // pinned, coherent: per-call gradient table
+  GradSeg* dev_h_grad = nullptr;     // its device address
   GradSeg* d_grad = nullptr;
-  hipEvent_t grad_event = nullptr;   // marks the upload of h_grad
-  bool grad_event_pending = false;
+  uint64_t grad_seq = 0;             // sequence number of the last fetch of h_grad enqueued
   bool shadow_valid = false;         // S holds what the score pass expects
 
   // state machine

@@ -39,6 +39,7 @@ static_assert(kPieceBytes % (16u * kCopyThreads) == 0, "pack tiling");
 constexpr uint32_t kRecordAlign = 256u;
 constexpr uint32_t kFinalizeThreads = 1024;
 constexpr uint32_t kSelectThreads = 256;  // beyond 64 layers
+constexpr uint32_t kTableThreads = 256;
 
 // Resident blocks per CU of the streaming kernels (0: as many as registers
 // and waves allow), held there by a dynamic LDS reservation the kernel never
@@ -180,6 +181,27 @@ struct SelectHeader {
 };
 static_assert(sizeof(SelectHeader) == 64, "header layout");
 
+// One rank of a restore: the layer, the address of its record, and the pieces
+// of the ranks before it (the entry behind the last holds their total).
+struct RankEntry {
+  uint64_t src;
+  uint64_t piece_prefix;
+  uint64_t layer;
+  uint64_t pad;
+};
+
+// Pinned host memory that small tables pass through, in both directions.
+// Followed by u, Delta and t_l of n_layers each (written by the device), then
+// n_layers + 1 RankEntry and n_layers steps of a restore (written by the host).  The numbers
+// are written last by the device: state_seq when the state is there, grad_seq
+// when the gradient table has been read.
+struct HostState {
+  uint64_t state_seq;
+  uint64_t grad_seq;
+  uint64_t reserved[6];
+};
+static_assert(sizeof(HostState) == 64, "tables stay 16-byte aligned");
+
 // Device-resident state of one context.
 struct DeviceTables {
   uint32_t n_layers;
@@ -209,10 +231,7 @@ struct DeviceTables {
   SelectHeader* host_result;          // pinned host memory (device address): header + mask[N]
   const OptSeg* opt_segs;             // [n_segments]
   const GradSeg* grad_segs;           // [n_segments], refreshed per optimizer call
-  // restore scratch
-  uint32_t* rank_layer;               // [N]
-  uint64_t* rank_src;                 // [N]
-  uint64_t* rank_piece_prefix;        // [N+1]
+  RankEntry* ranks;                   // [N+1] restore scratch
 };
 
 // Launchers: return hipGetLastError() of the launches.
@@ -222,6 +241,10 @@ hipError_t launch_score(const DeviceTables& t, hipStream_t st);
 hipError_t launch_finalize(const DeviceTables& t, hipStream_t st);
 hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, int base_mode, uint64_t seq,
                          hipStream_t st);
+// Small tables through pinned host memory (HostState): device addresses.
+hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st);
+hipError_t launch_push_state(const DeviceTables& t, HostState* host, uint64_t seq, hipStream_t st);
+hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, int64_t step, hipStream_t st);
 hipError_t launch_pack(const DeviceTables& t, uint32_t first_rank, uint32_t last_rank,
                        uint64_t piece_base, uint64_t n_pieces, uint64_t rec_base,
                        void* staging, int refresh_shadow, hipStream_t st);

@@ -341,6 +341,44 @@ __global__ __launch_bounds__(NT) void select_kernel(const DeviceTables t, int64_
   if (threadIdx.x == NT - 1) hr->seq = seq;
 }
 
+// ---- small tables between pinned host memory and the device ---------------------
+// One block each, beside the streaming kernels in the same stream: a copy
+// command of the runtime waits for its own engine or kernel and leaves gaps
+// of 6-20 us around it, and a copy back to the host a round trip each.
+
+// n 16-byte entries from pinned host memory; the flag tells the host that the
+// source may be written again.
+__global__ __launch_bounds__(kTableThreads) void fetch_kernel(const u32x4* src, u32x4* dst, uint32_t n, uint64_t* flag,
+                                                              uint64_t seq) {
+  for (uint32_t i = threadIdx.x; i < n; i += kTableThreads) dst[i] = src[i];
+  __syncthreads();  // every load has returned: its value was stored
+  if (threadIdx.x == 0 && flag) *reinterpret_cast<volatile uint64_t*>(flag) = seq;
+}
+
+// u, Delta and t_l of every layer to pinned host memory, then the number the
+// host waits for.
+__global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceTables t, HostState* h, uint64_t seq) {
+  const uint32_t N = t.n_layers;
+  double* u = reinterpret_cast<double*>(h + 1);
+  for (uint32_t l = threadIdx.x; l < N; l += kTableThreads) {
+    u[l] = t.u[l];
+    u[N + l] = t.delta[l];
+    reinterpret_cast<int64_t*>(u)[2 * N + l] = t.t_last[l];
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *reinterpret_cast<volatile uint64_t*>(&h->state_seq) = seq;
+}
+
+// Delta = 0 and t_l = steps[l] (or one step for all) of every layer.
+__global__ __launch_bounds__(kTableThreads) void reset_state_kernel(const DeviceTables t, const int64_t* steps,
+                                                                    int64_t step) {
+  for (uint32_t l = threadIdx.x; l < t.n_layers; l += kTableThreads) {
+    t.delta[l] = 0.0;
+    t.t_last[l] = steps ? steps[l] : step;
+  }
+}
+
 // ---- byte movement of one piece ----------------------------------------------
 // len bytes, a multiple of 2, from src to dst and, if given, to dst2, all at
 // least 2-byte aligned.  Full pieces go through buffer resources, the tails
@@ -446,7 +484,7 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(const DeviceTables t
 }
 
 // ---- unpack: composite restore from device-resident records --------------------
-// rank r restores layer rank_layer[r] from the record at address rank_src[r];
+// rank r restores layer ranks[r].layer from the record at address ranks[r].src;
 // every W block also refreshes the shadow.  An array's pieces start behind its
 // head, on a line of the array, so that the stores do not split lines; the
 // array's first piece takes the head with it, and the last may be empty.
@@ -454,12 +492,13 @@ __device__ __forceinline__ void unpack_piece(const DeviceTables& t, uint32_t n_r
   uint32_t lo = 0, hi = n_ranks;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (t.rank_piece_prefix[mid] <= q) lo = mid; else hi = mid;
+    if (t.ranks[mid].piece_prefix <= q) lo = mid; else hi = mid;
   }
-  const uint32_t l = t.rank_layer[lo];
-  const uint64_t lp = q - t.rank_piece_prefix[lo];
+  const RankEntry rank = t.ranks[lo];
+  const uint64_t l = rank.layer;
+  const uint64_t lp = q - rank.piece_prefix;
   const CopyUnit u = t.units[t.piece_unit[t.layer_piece_begin[l] + lp]];
-  const uint8_t* src = reinterpret_cast<const uint8_t*>(t.rank_src[lo]) + u.rec_off;
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(rank.src) + u.rec_off;
   uint8_t* dst = reinterpret_cast<uint8_t*>(u.arr);
   uint8_t* dst2 = u.shadow ? reinterpret_cast<uint8_t*>(u.shadow) : nullptr;
   const uint32_t p = static_cast<uint32_t>(lp) - u.piece0;
@@ -556,6 +595,22 @@ hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, i
   else
     hipLaunchKernelGGL(select_kernel<kSelectThreads>, dim3(1), dim3(kSelectThreads), 0, st, t, step, lr_scale, base_mode,
                        seq);
+  return hipGetLastError();
+}
+
+hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st) {
+  hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kTableThreads), 0, st, static_cast<const u32x4*>(host_src),
+                     static_cast<u32x4*>(dst), n16, flag, seq);
+  return hipGetLastError();
+}
+
+hipError_t launch_push_state(const DeviceTables& t, HostState* host, uint64_t seq, hipStream_t st) {
+  hipLaunchKernelGGL(push_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host, seq);
+  return hipGetLastError();
+}
+
+hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, int64_t step, hipStream_t st) {
+  hipLaunchKernelGGL(reset_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host_steps, step);
   return hipGetLastError();
 }
 

@@ -220,14 +220,14 @@ lc_status dev_alloc(lc_ctx* c, T** p, size_t count) {
   return LC_OK;
 }
 
-// Host vectors that feed asynchronous uploads must outlive the copies: a
-// function that uploads from locals holds one of these, so that an early
-// return (a failed call after some copies were enqueued) still waits for
-// the stream before the vectors go.  On the normal path the stream has
-// already been synchronised and the wait returns at once.
-struct UploadsDrained {
+// Copies out of a caller's host payload must not outlive the call: an early
+// return (a failed call after some copies were enqueued) still waits for them.
+struct StreamDrained {
   lc_ctx* c;
-  ~UploadsDrained() { (void)hipStreamSynchronize(c->stream); }
+  bool armed;
+  ~StreamDrained() {
+    if (armed) (void)hipStreamSynchronize(c->stream);
+  }
 };
 
 template <typename T>
@@ -244,8 +244,8 @@ void free_all(lc_ctx* c) {
   c->h_result = nullptr;
   if (c->h_grad) (void)hipHostFree(c->h_grad);
   c->h_grad = nullptr;
-  if (c->grad_event) (void)hipEventDestroy(c->grad_event);
-  c->grad_event = nullptr;
+  if (c->h_state) (void)hipHostFree(c->h_state);
+  c->h_state = nullptr;
 }
 
 lc_status check_ctx(lc_ctx* c) {
@@ -254,32 +254,55 @@ lc_status check_ctx(lc_ctx* c) {
   return LC_OK;
 }
 
-// Wait until the select kernel has written the pending selection into the
-// pinned host mirror (its sequence number appears last, after a system-scope
-// fence).  The flag is polled, so the host reacts within a microsecond or two
+// Wait for a number that a kernel of the stream writes into pinned host
+// memory.  The flag is polled, so the host reacts within a microsecond or two
 // of the kernel's store instead of after a device-to-host copy and a stream
-// synchronisation; every 256 polls the stream is queried, so an error or a
-// stream that drained without the flag ends the wait.
-lc_status wait_result(lc_ctx* c) {
-  const volatile uint64_t* flag = &c->h_result->seq;
+// synchronisation; every 256 polls the stream is queried, so an error ends the
+// wait, and so does a stream that drained without the number (`drained`).
+hipError_t wait_number(lc_ctx* c, const uint64_t* number, uint64_t want, bool* drained) {
+  const volatile uint64_t* flag = number;
+  *drained = false;
   for (uint32_t spin = 1;; ++spin) {
-    if (*flag == c->result_seq) break;
+    if (*flag == want) break;
     if (spin % 256 == 0) {
       const hipError_t q = hipStreamQuery(c->stream);
       if (q == hipSuccess) {
-        if (*flag == c->result_seq) break;
-        c->poisoned = true;
-        return fail(LC_ERR_HIP, "the selection never reached the host");
+        *drained = *flag != want;
+        break;
       }
       if (q != hipErrorNotReady) {
         (void)hipGetLastError();
         c->poisoned = true;
-        return fail(LC_ERR_HIP, "waiting for the selection failed: %s", hipGetErrorString(q));
+        return q;
       }
     }
   }
   std::atomic_thread_fence(std::memory_order_acquire);
+  return hipSuccess;
+}
+
+// Wait until the select kernel has written the pending selection into the
+// pinned host memory (its sequence number appears last, after system-scope
+// fences).
+lc_status wait_result(lc_ctx* c) {
+  bool drained = false;
+  const hipError_t e = wait_number(c, &c->h_result->seq, c->result_seq, &drained);
+  if (e != hipSuccess) return fail(LC_ERR_HIP, "waiting for the selection failed: %s", hipGetErrorString(e));
+  if (drained) {
+    c->poisoned = true;
+    return fail(LC_ERR_HIP, "the selection never reached the host");
+  }
   return LC_OK;
+}
+
+// The parts of the pinned memory behind HostState.
+RankEntry* state_ranks(const lc_ctx* c, HostState* h) {
+  return reinterpret_cast<RankEntry*>(reinterpret_cast<uint8_t*>(h + 1) +
+                                      round_up(3ull * sizeof(double) * c->L.N, 64));
+}
+int64_t* state_steps(const lc_ctx* c, HostState* h) { return reinterpret_cast<int64_t*>(state_ranks(c, h) + c->L.N + 1); }
+uint64_t state_bytes(uint64_t n) {
+  return sizeof(HostState) + round_up(3 * sizeof(double) * n, 64) + (n + 1) * sizeof(RankEntry) + n * sizeof(int64_t);
 }
 
 // Make the pending selection's mask available on the host.
@@ -386,13 +409,8 @@ lc_status restore_range_from_host(lc_ctx* c, uint32_t l, uint64_t rec_off, uint6
 }
 
 lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& steps) {
-  const uint32_t N = c->L.N;
-  std::vector<double> zeros(N, 0.0);
-  UploadsDrained drained{c};
-  lc_status st = upload(c, c->dt.delta, zeros);
-  if (st != LC_OK) return st;
-  st = upload(c, c->dt.t_last, steps);
-  if (st != LC_OK) return st;
+  std::memcpy(state_steps(c, c->h_state), steps.data(), c->L.N * sizeof(int64_t));
+  LC_HIP(c, launch_reset_state(c->dt, state_steps(c, c->dev_h_state), 0, c->stream));
   LC_HIP(c, hipStreamSynchronize(c->stream));
   c->last_step = t_fail;
   c->scored = false;
@@ -523,7 +541,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   ScoreSeg* segs; uint32_t* chunk_seg; uint32_t* lcb; double2* partials; double* u; double* delta;
   int64_t* t_last; double* k0; uint64_t* numel; uint64_t* rec; uint64_t* lpieces; CopyUnit* units;
   uint32_t* piece_unit; uint64_t* lpb; uint32_t* sel_layer; uint64_t* srp; uint64_t* spp;
-  uint32_t* rank_layer; uint64_t* rank_src; uint64_t* rpp;
+  RankEntry* ranks;
   LC_TRY(dev_alloc(c, &segs, L.score_segs.size()));
   LC_TRY(dev_alloc(c, &chunk_seg, L.chunk_seg.size()));
   LC_TRY(dev_alloc(c, &lcb, N + 1));
@@ -544,42 +562,36 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   OptSeg* opt_segs;
   LC_TRY(dev_alloc(c, &opt_segs, L.opt_segs.size()));
   LC_TRY(dev_alloc(c, &c->d_grad, L.opt_segs.size()));
-  LC_TRY(dev_alloc(c, &rank_layer, N));
-  LC_TRY(dev_alloc(c, &rank_src, N));
-  LC_TRY(dev_alloc(c, &rpp, N + 1));
+  LC_TRY(dev_alloc(c, &ranks, N + 1));
   {
-    // the select kernel writes this mirror itself: coherent (fine-grained)
-    // pinned memory, so its stores reach the host without a copy
-    void* h = nullptr;
-    hipError_t e = hipHostMalloc(&h, sizeof(SelectHeader) + N, hipHostMallocCoherent);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return bail(fail(LC_ERR_OOM, "hipHostMalloc failed: %s", hipGetErrorString(e)));
-    }
-    c->h_result = static_cast<SelectHeader*>(h);
-    std::memset(h, 0, sizeof(SelectHeader) + N);
-    void* dh = nullptr;
-    e = hipHostGetDevicePointer(&dh, h, 0);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return bail(fail(LC_ERR_HIP, "hipHostGetDevicePointer failed: %s", hipGetErrorString(e)));
-    }
-    t.host_result = static_cast<SelectHeader*>(dh);
-    h = nullptr;
-    e = hipHostMalloc(&h, sizeof(GradSeg) * L.opt_segs.size(), hipHostMallocDefault);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return bail(fail(LC_ERR_OOM, "hipHostMalloc failed: %s", hipGetErrorString(e)));
-    }
-    c->h_grad = static_cast<GradSeg*>(h);
-    e = hipEventCreateWithFlags(&c->grad_event, hipEventDisableTiming);
-    if (e != hipSuccess) return bail(fail(LC_ERR_HIP, "hipEventCreate failed: %s", hipGetErrorString(e)));
+    // kernels write and read these themselves: coherent (fine-grained) pinned
+    // memory, so the stores reach the other side without a copy
+    auto pinned = [&](uint64_t bytes, auto** host, auto** dev) -> lc_status {
+      void *h = nullptr, *dh = nullptr;
+      hipError_t e = hipHostMalloc(&h, bytes, hipHostMallocCoherent);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(LC_ERR_OOM, "hipHostMalloc failed: %s", hipGetErrorString(e));
+      }
+      *host = static_cast<std::remove_reference_t<decltype(**host)>*>(h);
+      std::memset(h, 0, bytes);
+      e = hipHostGetDevicePointer(&dh, h, 0);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(LC_ERR_HIP, "hipHostGetDevicePointer failed: %s", hipGetErrorString(e));
+      }
+      *dev = static_cast<std::remove_reference_t<decltype(**dev)>*>(dh);
+      return LC_OK;
+    };
+    LC_TRY(pinned(sizeof(SelectHeader) + N, &c->h_result, &t.host_result));
+    LC_TRY(pinned(state_bytes(N), &c->h_state, &c->dev_h_state));
+    LC_TRY(pinned(sizeof(GradSeg) * L.opt_segs.size(), &c->h_grad, &c->dev_h_grad));
   }
   t.segs = segs; t.chunk_seg = chunk_seg; t.layer_chunk_begin = lcb; t.partials = partials;
   t.u = u; t.delta = delta; t.t_last = t_last; t.k0 = k0; t.numel = numel; t.rec_bytes = rec;
   t.layer_pieces = lpieces; t.units = units; t.piece_unit = piece_unit; t.layer_piece_begin = lpb;
   t.sel_layer = sel_layer; t.sel_rec_prefix = srp; t.sel_piece_prefix = spp;
-  t.rank_layer = rank_layer; t.rank_src = rank_src; t.rank_piece_prefix = rpp;
+  t.ranks = ranks;
   t.opt_segs = opt_segs; t.grad_segs = c->d_grad;
 
   std::vector<double> zeros(N, 0.0), k0v(d->k0, d->k0 + N);
@@ -756,8 +768,8 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
   // record address of each layer, and where each version's payload lives
   std::vector<int> kind(n_versions, -1);  // 0 device, 1 host
   std::vector<const uint8_t*> dev_base(n_versions, nullptr);
-  std::vector<uint32_t> rank_layer;
-  std::vector<uint64_t> rank_src, rank_pp(1, 0);
+  std::vector<RankEntry> ranks;
+  uint64_t pieces = 0;
   std::vector<std::pair<uint32_t, const uint8_t*>> host_layers;
   for (uint32_t l = 0; l < N; ++l) {
     const uint32_t i = static_cast<uint32_t>(choice[l]);
@@ -778,24 +790,21 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
     for (uint32_t j = 0; j < l; ++j)
       if (v[i].mask[j]) off += L.rec_bytes[j];
     if (kind[i] == 0) {
-      rank_layer.push_back(l);
-      rank_src.push_back(reinterpret_cast<uint64_t>(dev_base[i] + off));
-      rank_pp.push_back(rank_pp.back() + L.layer_pieces[l]);
+      ranks.push_back({reinterpret_cast<uint64_t>(dev_base[i] + off), pieces, l, 0});
+      pieces += L.layer_pieces[l];
     } else {
       host_layers.emplace_back(l, static_cast<const uint8_t*>(v[i].payload) + off);
     }
   }
-  UploadsDrained drained{c};  // declared after the tables it protects, so it runs first
-  if (!rank_layer.empty()) {
-    st = upload(c, c->dt.rank_layer, rank_layer);
-    if (st != LC_OK) return st;
-    st = upload(c, c->dt.rank_src, rank_src);
-    if (st != LC_OK) return st;
-    st = upload(c, c->dt.rank_piece_prefix, rank_pp);
-    if (st != LC_OK) return st;
-    const uint64_t pieces = rank_pp.back();
-    LC_HIP(c, launch_unpack(c->dt, static_cast<uint32_t>(rank_layer.size()), pieces, c->stream));
+  if (!ranks.empty()) {
+    const uint32_t n_ranks = static_cast<uint32_t>(ranks.size());
+    ranks.push_back({0, pieces, 0, 0});
+    std::memcpy(state_ranks(c, c->h_state), ranks.data(), ranks.size() * sizeof(RankEntry));
+    LC_HIP(c, launch_fetch(state_ranks(c, c->dev_h_state), c->dt.ranks,
+                           static_cast<uint32_t>(ranks.size() * (sizeof(RankEntry) / 16)), nullptr, 0, c->stream));
+    LC_HIP(c, launch_unpack(c->dt, n_ranks, pieces, c->stream));
   }
+  StreamDrained drained{c, true};
   // host-resident records: one copy per block, then S <- W
   for (const auto& hl : host_layers) {
     st = restore_range_from_host(c, hl.first, 0, L.rec_bytes[hl.first], hl.second);
@@ -805,6 +814,7 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
   for (uint32_t l = 0; l < N; ++l) steps[l] = v[choice[l]].step;
   st = restore_finish(c, t_fail, steps);
   if (st != LC_OK) return st;
+  drained.armed = false;
   if (chosen_step_out) std::memcpy(chosen_step_out, steps.data(), N * sizeof(int64_t));
   return LC_OK;
 }
@@ -816,14 +826,7 @@ lc_status lc_rebase(lc_ctx* c, int64_t step) {
   if (step < c->last_step)
     return fail(LC_ERR_BAD_STATE, "the base step %lld precedes the last step %lld", static_cast<long long>(step),
                 static_cast<long long>(c->last_step));
-  const uint32_t N = c->L.N;
-  std::vector<double> zeros(N, 0.0);
-  std::vector<int64_t> tl(N, step);
-  UploadsDrained drained{c};
-  st = upload(c, c->dt.delta, zeros);
-  if (st != LC_OK) return st;
-  st = upload(c, c->dt.t_last, tl);
-  if (st != LC_OK) return st;
+  LC_HIP(c, launch_reset_state(c->dt, nullptr, step, c->stream));
   for (const lc_segment& sg : c->L.segs) {
     if (!c->L.has_shadow) break;
     LC_HIP(c, hipMemcpyAsync(sg.shadow, sg.weight, sg.numel * c->L.esz, hipMemcpyDeviceToDevice, c->stream));
@@ -831,7 +834,6 @@ lc_status lc_rebase(lc_ctx* c, int64_t step) {
   c->shadow_valid = c->L.has_shadow;
   st = enqueue_select(c, step, 1.0, 1, true);
   if (st != LC_OK) return st;
-  // the uploads read host vectors that end with this call
   LC_HIP(c, hipStreamSynchronize(c->stream));
   c->last_step = step;
   c->scored = false;
@@ -864,17 +866,20 @@ lc_status optimizer_begin(lc_ctx* c, int64_t step, const void* const* grads, int
     if (g % gsz) return fail(LC_ERR_INVALID_ARG, "gradient of segment %zu is misaligned", i);
     if (decay_mask && decay_mask[i] > 1) return fail(LC_ERR_INVALID_ARG, "decay_mask must be 0/1");
   }
-  // the pinned table may still feed the previous call's upload
-  if (c->grad_event_pending) LC_HIP(c, hipEventSynchronize(c->grad_event));
+  // the pinned table may still feed the previous call's fetch (a stream that
+  // has drained has none under way)
+  bool drained = false;
+  if (c->grad_seq) LC_HIP(c, wait_number(c, &c->h_state->grad_seq, c->grad_seq, &drained));
   for (size_t i = 0; i < ns; ++i) {
     const uint64_t g = reinterpret_cast<uint64_t>(grads[i]);
     c->h_grad[i].grad = g;
     c->h_grad[i].decay = decay_mask ? decay_mask[i] : 1u;
     c->h_grad[i].vec_ok = g % (4 * gsz) == 0 ? 1u : 0u;
   }
-  LC_HIP(c, hipMemcpyAsync(c->d_grad, c->h_grad, sizeof(GradSeg) * ns, hipMemcpyHostToDevice, c->stream));
-  LC_HIP(c, hipEventRecord(c->grad_event, c->stream));
-  c->grad_event_pending = true;
+  static_assert(sizeof(GradSeg) == 16, "one entry a lane");
+  ++c->grad_seq;
+  LC_HIP(c, launch_fetch(c->dev_h_grad, c->d_grad, static_cast<uint32_t>(ns), &c->dev_h_state->grad_seq, c->grad_seq,
+                         c->stream));
   return LC_OK;
 }
 
@@ -948,10 +953,19 @@ lc_status lc_read_state(lc_ctx* c, double* u_out, double* delta_out, int64_t* t_
   lc_status st = check_ctx(c);
   if (st != LC_OK) return st;
   const size_t N = c->L.N;
-  LC_HIP(c, hipStreamSynchronize(c->stream));
-  if (u_out) LC_HIP(c, hipMemcpy(u_out, c->dt.u, N * sizeof(double), hipMemcpyDeviceToHost));
-  if (delta_out) LC_HIP(c, hipMemcpy(delta_out, c->dt.delta, N * sizeof(double), hipMemcpyDeviceToHost));
-  if (t_last_out) LC_HIP(c, hipMemcpy(t_last_out, c->dt.t_last, N * sizeof(int64_t), hipMemcpyDeviceToHost));
+  // a kernel behind all enqueued work writes the state into pinned memory
+  ++c->state_seq;
+  LC_HIP(c, launch_push_state(c->dt, c->dev_h_state, c->state_seq, c->stream));
+  bool drained = false;
+  LC_HIP(c, wait_number(c, &c->h_state->state_seq, c->state_seq, &drained));
+  if (drained) {
+    c->poisoned = true;
+    return fail(LC_ERR_HIP, "the state never reached the host");
+  }
+  const double* h = reinterpret_cast<const double*>(c->h_state + 1);
+  if (u_out) std::memcpy(u_out, h, N * sizeof(double));
+  if (delta_out) std::memcpy(delta_out, h + N, N * sizeof(double));
+  if (t_last_out) std::memcpy(t_last_out, h + 2 * N, N * sizeof(int64_t));
   return LC_OK;
 }
 
