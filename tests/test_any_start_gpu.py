@@ -159,5 +159,23 @@ def test_segments_at_any_element(dtype, master, op, offsets):
         chosen = LC.lc_restore_composite(ctx, versions, 1, N)
         assert chosen.tolist() == orc.restore(host, 1).tolist()
         check("restore")
+        # the same from host memory: page-locked (a kernel reads it), at odd places of one allocation, and pageable
+        pinned = torch.empty(sum(h["payload"].nbytes + 256 for h in host), dtype=torch.uint8, pin_memory=True)
+        for where in ("pinned", "pageable"):
+            at, hv = 2, []
+            for h in host:
+                k = h["payload"].nbytes
+                if where == "pinned":
+                    buf = pinned[at:at + k]
+                    buf.copy_(torch.from_numpy(h["payload"].copy()))
+                    at += k + 254
+                else:
+                    buf = torch.from_numpy(h["payload"].copy())
+                hv.append({"step": h["step"], "mask": h["mask"], "payload": buf.data_ptr(), "payload_bytes": k, "keep": buf})
+            for d in segs:
+                for a in arrays:
+                    d[a].buf[d[a].off:d[a].off + d[a].host.nbytes] = 0x33
+            assert LC.lc_restore_composite(ctx, hv, 1, N).tolist() == chosen.tolist()
+            check(f"restore from {where} memory")
     finally:
         LC.lc_destroy(ctx)
