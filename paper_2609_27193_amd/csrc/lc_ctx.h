@@ -107,5 +107,21 @@ lc_status restore_range_from_host(lc_ctx* c, uint32_t layer, uint64_t rec_off, u
 // allocation, as far as HIP can tell: pointers a kernel or a device copy
 // could only fault on are refused before any work is enqueued.
 bool device_range_ok(const void* p, uint64_t bytes);
+// The same for many arrays of one call: an array inside an allocation that
+// this call has looked up before needs no lookup of its own (0.45 us each, two
+// of them: 438 arrays cost 170 us).  Lives no longer than the call.
+class DeviceRanges {
+ public:
+  bool ok(const void* p, uint64_t bytes);
+
+ private:
+  struct Range {
+    uintptr_t base;
+    uint64_t size;
+  };
+  static constexpr size_t kLookBack = 15;  // allocations tried before a lookup
+  std::vector<Range> seen_;  // most of a layout's arrays lie in a few allocations
+  size_t last_ = 0;
+};
 lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& steps);
 }  // namespace lc

@@ -46,18 +46,20 @@ void* g_scratch_ptr[kMaxDevices] = {};
 
 uint64_t align256(uint64_t x) { return (x + 255) / 256 * 256; }
 
-// Scratch layout of one batch of ns segments, nc chunks and nl layers.
+// Scratch layout of one batch of ns segments, nc chunks and nl layers.  The
+// tables that the host makes (up to `host_end`) come first, for one upload.
 struct Regions {
-  uint64_t segs, chunk_seg, lcb, numel, partials, delta, end;
+  uint64_t segs, lcb, numel, host_end, chunk_seg, partials, delta, end;
 };
 
 Regions regions(uint64_t ns, uint64_t nc, uint64_t nl) {
   Regions r;
   r.segs = 0;
-  r.chunk_seg = r.segs + align256(ns * sizeof(ScoreSeg));
-  r.lcb = r.chunk_seg + align256(nc * sizeof(uint32_t));
+  r.lcb = r.segs + align256(ns * sizeof(ScoreSeg));
   r.numel = r.lcb + align256((nl + 1) * sizeof(uint32_t));
-  r.partials = r.numel + align256(nl * sizeof(uint64_t));
+  r.host_end = r.numel + align256(nl * sizeof(uint64_t));
+  r.chunk_seg = r.host_end;
+  r.partials = r.chunk_seg + align256(nc * sizeof(uint32_t));
   r.delta = r.partials + align256(nc * sizeof(double2));
   r.end = r.delta + align256(nl * sizeof(double));
   return r;
@@ -95,9 +97,7 @@ __global__ __launch_bounds__(256) void chunk_table_kernel(const ScoreSeg* segs, 
 struct Batch {
   uint32_t s0, s1, l0, l1;
   uint64_t chunks;
-  std::vector<ScoreSeg> segs;
-  std::vector<uint32_t> lcb;
-  std::vector<uint64_t> numel;
+  std::vector<uint8_t> tables;  // the regions up to host_end
 };
 
 // Host tables feed asynchronous copies: wait for the stream before they go,
@@ -187,9 +187,10 @@ extern "C" lc_status lc_score_layers_static(const lc_segment* segments, uint32_t
     }
     if (sdev != dev) return fail(LC_ERR_INVALID_ARG, "the stream belongs to device %d, not the current %d", sdev, dev);
   }
+  DeviceRanges known;
   for (uint32_t i = 0; i < n_segments; ++i) {
     const lc_segment& s = segments[i];
-    if (!device_range_ok(s.weight, s.numel * esz) || !device_range_ok(s.shadow, s.numel * esz))
+    if (!known.ok(s.weight, s.numel * esz) || !known.ok(s.shadow, s.numel * esz))
       return fail(LC_ERR_INVALID_ARG, "segment %u: weight or shadow is not device memory of %llu elements", i,
                   static_cast<unsigned long long>(s.numel));
   }
@@ -201,19 +202,19 @@ extern "C" lc_status lc_score_layers_static(const lc_segment* segments, uint32_t
 
   // ---- tables and kernels, one batch after the other on the caller's stream --------
   for (Batch& b : batches) {
+    const Regions r = regions(b.s1 - b.s0, b.chunks, b.l1 - b.l0);
+    b.tables.assign(r.host_end, 0);
+    ScoreSeg* segs = reinterpret_cast<ScoreSeg*>(b.tables.data() + r.segs);
+    uint32_t* lcb = reinterpret_cast<uint32_t*>(b.tables.data() + r.lcb);
+    uint64_t* numel = reinterpret_cast<uint64_t*>(b.tables.data() + r.numel);
     uint32_t c = 0;
     for (uint32_t i = b.s0; i < b.s1; ++i) {
       const lc_segment& s = segments[i];
-      b.segs.push_back(
-          score_seg(reinterpret_cast<uint64_t>(s.weight), reinterpret_cast<uint64_t>(s.shadow), s.numel, esz, c));
+      segs[i - b.s0] =
+          score_seg(reinterpret_cast<uint64_t>(s.weight), reinterpret_cast<uint64_t>(s.shadow), s.numel, esz, c);
       c += static_cast<uint32_t>((s.numel + ce - 1) / ce);
-    }
-    b.lcb.assign(1, 0);
-    for (uint32_t l = b.l0; l < b.l1; ++l) {
-      b.lcb.push_back(b.lcb.back() + static_cast<uint32_t>(layer_chunks[l]));
-      uint64_t n = 0;
-      for (uint32_t i = seg_begin[l]; i < seg_begin[l + 1]; ++i) n += segments[i].numel;
-      b.numel.push_back(n);
+      numel[s.layer - b.l0] += s.numel;
+      lcb[s.layer - b.l0 + 1] = c;
     }
   }
   DrainOnExit drain{st};
@@ -235,11 +236,7 @@ extern "C" lc_status lc_score_layers_static(const lc_segment* segments, uint32_t
     t.delta = reinterpret_cast<double*>(base + r.delta);
     t.u = u_out + b.l0;
     drain.armed = true;
-    hipError_t e = hipMemcpyAsync(base + r.segs, b.segs.data(), ns * sizeof(ScoreSeg), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(base + r.lcb, b.lcb.data(), b.lcb.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(base + r.numel, b.numel.data(), nl * sizeof(uint64_t), hipMemcpyHostToDevice, st);
+    hipError_t e = hipMemcpyAsync(base, b.tables.data(), r.host_end, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) {
       hipLaunchKernelGGL(chunk_table_kernel, dim3(ns), dim3(256), 0, st, t.segs,
                          reinterpret_cast<uint32_t*>(base + r.chunk_seg), t.n_chunks);

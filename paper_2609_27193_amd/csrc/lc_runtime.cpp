@@ -370,8 +370,9 @@ lc_status require_packed(lc_ctx* c) {
 
 namespace lc {
 
-bool device_range_ok(const void* p, uint64_t bytes) {
-  if (!p) return false;
+// Looks p up: whether it is device (or managed) memory, and the allocation it
+// lies in (size 0: the extent is not known, a virtual-memory mapping, say).
+static bool find_device_range(const void* p, uintptr_t* base_out, uint64_t* size_out) {
   hipPointerAttribute_t attr;
   if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
     (void)hipGetLastError();
@@ -382,10 +383,42 @@ bool device_range_ok(const void* p, uint64_t bytes) {
   size_t size = 0;
   if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
     (void)hipGetLastError();
-    return true;  // the extent is not known (a virtual-memory mapping, say): the type check stands
+    size = 0;
   }
-  const uintptr_t b = reinterpret_cast<uintptr_t>(base), q = reinterpret_cast<uintptr_t>(p);
-  return q >= b && q - b <= size && bytes <= size - (q - b);
+  *base_out = reinterpret_cast<uintptr_t>(base);
+  *size_out = size;
+  return true;
+}
+
+static bool inside(uintptr_t q, uint64_t bytes, uintptr_t base, uint64_t size) {
+  return q >= base && q - base <= size && bytes <= size - (q - base);
+}
+
+bool device_range_ok(const void* p, uint64_t bytes) {
+  uintptr_t base = 0;
+  uint64_t size = 0;
+  if (!p || !find_device_range(p, &base, &size)) return false;
+  return size == 0 || inside(reinterpret_cast<uintptr_t>(p), bytes, base, size);
+}
+
+bool DeviceRanges::ok(const void* p, uint64_t bytes) {
+  if (!p) return false;
+  const uintptr_t q = reinterpret_cast<uintptr_t>(p);
+  for (size_t k = 0; k < seen_.size(); ++k) {  // from the allocation of the last array on
+    const size_t i = (last_ + k) % seen_.size();
+    if (q >= seen_[i].base && q - seen_[i].base < seen_[i].size) {
+      last_ = i;
+      return inside(q, bytes, seen_[i].base, seen_[i].size);
+    }
+    if (k == kLookBack) break;
+  }
+  Range r{0, 0};
+  if (!find_device_range(p, &r.base, &r.size)) return false;
+  if (r.size == 0) return true;
+  if (!inside(q, bytes, r.base, r.size)) return false;
+  seen_.push_back(r);
+  last_ = seen_.size() - 1;
+  return true;
 }
 
 // Whether a kernel can read [p, p + bytes): all of it in one allocation of
@@ -511,6 +544,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   }
   // every array a kernel will stream must be device memory of its full
   // extent: refused here rather than faulting in a kernel
+  lc::DeviceRanges ranges;
   for (uint32_t i = 0; i < c->L.segs.size(); ++i) {
     const lc_segment& sg = c->L.segs[i];
     const void* arr[5] = {sg.weight, sg.shadow, sg.master, sg.exp_avg, sg.exp_avg_sq};
@@ -518,7 +552,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
     for (int a = 0; a < 5; ++a) {
       if (!arr[a]) continue;
       const uint64_t bytes = sg.numel * (a < 2 ? c->L.esz : 4u);
-      if (!device_range_ok(arr[a], bytes)) {
+      if (!ranges.ok(arr[a], bytes)) {
         delete c;
         return fail(LC_ERR_INVALID_ARG, "segment %u: %s is not device memory holding %llu bytes", i, kName[a],
                     static_cast<unsigned long long>(bytes));
