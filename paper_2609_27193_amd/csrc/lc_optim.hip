@@ -253,14 +253,18 @@ __device__ __forceinline__ void optim_elem(const OptSeg& sg, const GradSeg& gs, 
   b += static_cast<double>(fabsf(po));
 }
 
+typedef __attribute__((address_space(4))) GradSeg c_GradSeg;
+
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
-__device__ __forceinline__ void optim_chunk(const DeviceTables& t, const SC& sc, uint32_t c) {
+__device__ __forceinline__ void optim_chunk(const DeviceTables& t, const InlineGrads& ig, const SC& sc, uint32_t c) {
   constexpr uint32_t WSZ = WDT == 1 ? 2 : 4, GSZ = GDT == 1 ? 2 : 4;
   constexpr uint32_t CE = kChunkBytes / WSZ;  // elements per chunk (the score chunks)
   const uint32_t tid = threadIdx.x;
   const uint32_t si = t.chunk_seg[c];
   const OptSeg sg = t.opt_segs[si];
-  const GradSeg gs = t.grad_segs[si];
+  // a constant either way, so that the lookup stays a scalar load
+  const c_GradSeg* gt = (const c_GradSeg*)(t.grad_segs ? t.grad_segs : ig.g);
+  const GradSeg gs{gt[si].grad, gt[si].decay, gt[si].vec_ok};
   const uint32_t k = c - sg.chunk_begin;
   const uint64_t e0 = static_cast<uint64_t>(k) * CE + sg.head;  // the chunk's tile
   const uint64_t rem = sg.numel > e0 ? sg.numel - e0 : 0;
@@ -296,15 +300,16 @@ __device__ __forceinline__ void optim_chunk(const DeviceTables& t, const SC& sc,
 }
 
 template <int OPT, int WDT, int GDT, bool MASTER, bool LOOP, typename SC>
-__global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const DeviceTables t, const SC sc) {
+__global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const DeviceTables t, const SC sc,
+                                                                           const InlineGrads ig) {
   if constexpr (!LOOP) {
-    optim_chunk<OPT, WDT, GDT, MASTER>(t, sc, remap_xcd(blockIdx.x, gridDim.x));
+    optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, remap_xcd(blockIdx.x, gridDim.x));
   } else {
     for (uint64_t base = 0; base < t.n_chunks; base += gridDim.x) {
       const uint64_t left = t.n_chunks - base;
       const uint32_t span = left < gridDim.x ? static_cast<uint32_t>(left) : gridDim.x;
       if (blockIdx.x >= span) return;
-      optim_chunk<OPT, WDT, GDT, MASTER>(t, sc, static_cast<uint32_t>(base + remap_xcd(blockIdx.x, span)));
+      optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, static_cast<uint32_t>(base + remap_xcd(blockIdx.x, span)));
       __syncthreads();
     }
   }
@@ -325,7 +330,7 @@ __global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const
 constexpr uint32_t kOptBytesPerCU = 100 * 1024;
 
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
-void launch_optim_t(const DeviceTables& t, const SC& sc, hipStream_t st) {
+void launch_optim_t(const DeviceTables& t, const InlineGrads& ig, const SC& sc, hipStream_t st) {
   const uint32_t g = grid_for(t.n_chunks, kOptThreads<WDT, MASTER>);
   constexpr uint32_t CE = kChunkBytes / (WDT == 1 ? 2 : 4);
   constexpr uint32_t wsz = WDT == 1 ? 2 : 4;
@@ -335,33 +340,35 @@ void launch_optim_t(const DeviceTables& t, const SC& sc, hipStream_t st) {
                               : tile >= kOptBytesPerCU ? 1 : fit < 2 ? 2 : fit;
   const uint32_t lds = occupancy_lds(blocks);
   if (g == t.n_chunks)
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc, ig);
   else
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc, ig);
 }
 
 template <int OPT, typename SC>
-void launch_optim(const DeviceTables& t, int grad_dtype, int has_master, const SC& sc, hipStream_t st) {
+void launch_optim(const DeviceTables& t, const InlineGrads& ig, int grad_dtype, int has_master, const SC& sc,
+                  hipStream_t st) {
   const bool gb = grad_dtype == 1;
   if (t.dtype == 1) {
-    if (has_master) { if (gb) launch_optim_t<OPT, 1, 1, true>(t, sc, st); else launch_optim_t<OPT, 1, 2, true>(t, sc, st); }
-    else { if (gb) launch_optim_t<OPT, 1, 1, false>(t, sc, st); else launch_optim_t<OPT, 1, 2, false>(t, sc, st); }
+    if (has_master) { if (gb) launch_optim_t<OPT, 1, 1, true>(t, ig, sc, st); else launch_optim_t<OPT, 1, 2, true>(t, ig, sc, st); }
+    else { if (gb) launch_optim_t<OPT, 1, 1, false>(t, ig, sc, st); else launch_optim_t<OPT, 1, 2, false>(t, ig, sc, st); }
   } else {
-    if (has_master) { if (gb) launch_optim_t<OPT, 2, 1, true>(t, sc, st); else launch_optim_t<OPT, 2, 2, true>(t, sc, st); }
-    else { if (gb) launch_optim_t<OPT, 2, 1, false>(t, sc, st); else launch_optim_t<OPT, 2, 2, false>(t, sc, st); }
+    if (has_master) { if (gb) launch_optim_t<OPT, 2, 1, true>(t, ig, sc, st); else launch_optim_t<OPT, 2, 2, true>(t, ig, sc, st); }
+    else { if (gb) launch_optim_t<OPT, 2, 1, false>(t, ig, sc, st); else launch_optim_t<OPT, 2, 2, false>(t, ig, sc, st); }
   }
 }
 
 }  // namespace
 
-hipError_t launch_adamw(const DeviceTables& t, int grad_dtype, int has_master, const AdamScalars& sc,
-                        hipStream_t st) {
-  launch_optim<kAdamW>(t, grad_dtype, has_master, sc, st);
+hipError_t launch_adamw(const DeviceTables& t, const InlineGrads& grads, int grad_dtype, int has_master,
+                        const AdamScalars& sc, hipStream_t st) {
+  launch_optim<kAdamW>(t, grads, grad_dtype, has_master, sc, st);
   return hipGetLastError();
 }
 
-hipError_t launch_sgd(const DeviceTables& t, int grad_dtype, int has_master, const SgdScalars& sc, hipStream_t st) {
-  launch_optim<kSGD>(t, grad_dtype, has_master, sc, st);
+hipError_t launch_sgd(const DeviceTables& t, const InlineGrads& grads, int grad_dtype, int has_master,
+                      const SgdScalars& sc, hipStream_t st) {
+  launch_optim<kSGD>(t, grads, grad_dtype, has_master, sc, st);
   return hipGetLastError();
 }
 

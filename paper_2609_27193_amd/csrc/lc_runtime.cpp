@@ -610,7 +610,6 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   LC_TRY(dev_alloc(c, &spp, N + 1));
   OptSeg* opt_segs;
   LC_TRY(dev_alloc(c, &opt_segs, L.opt_segs.size()));
-  LC_TRY(dev_alloc(c, &c->d_grad, L.opt_segs.size()));
   LC_TRY(dev_alloc(c, &ranks, N + 1));
   {
     // kernels write and read these themselves: coherent (fine-grained) pinned
@@ -634,7 +633,10 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
     };
     LC_TRY(pinned(sizeof(SelectHeader) + N, &c->h_result, &t.host_result));
     LC_TRY(pinned(state_bytes(N), &c->h_state, &c->dev_h_state));
-    LC_TRY(pinned(sizeof(GradSeg) * L.opt_segs.size(), &c->h_grad, &c->dev_h_grad));
+    if (L.opt_segs.size() > kInlineGrads) {
+      LC_TRY(pinned(sizeof(GradSeg) * L.opt_segs.size(), &c->h_grad, &c->dev_h_grad));
+      LC_TRY(dev_alloc(c, &c->d_grad, L.opt_segs.size()));
+    }
   }
   t.segs = segs; t.chunk_seg = chunk_seg; t.layer_chunk_begin = lcb; t.partials = partials;
   t.u = u; t.delta = delta; t.t_last = t_last; t.k0 = k0; t.numel = numel; t.rec_bytes = rec;
@@ -921,20 +923,24 @@ lc_status optimizer_begin(lc_ctx* c, int64_t step, const void* const* grads, int
     if (g % gsz) return fail(LC_ERR_INVALID_ARG, "gradient of segment %zu is misaligned", i);
     if (decay_mask && decay_mask[i] > 1) return fail(LC_ERR_INVALID_ARG, "decay_mask must be 0/1");
   }
+  const bool fetched = ns > kInlineGrads;
   // the pinned table may still feed the previous call's fetch (a stream that
   // has drained has none under way)
   bool drained = false;
-  if (c->grad_seq) LC_HIP(c, wait_number(c, &c->h_state->grad_seq, c->grad_seq, &drained));
+  if (fetched && c->grad_seq) LC_HIP(c, wait_number(c, &c->h_state->grad_seq, c->grad_seq, &drained));
+  GradSeg* table = fetched ? c->h_grad : c->inline_grads.g;
   for (size_t i = 0; i < ns; ++i) {
     const uint64_t g = reinterpret_cast<uint64_t>(grads[i]);
-    c->h_grad[i].grad = g;
-    c->h_grad[i].decay = decay_mask ? decay_mask[i] : 1u;
-    c->h_grad[i].vec_ok = g % (4 * gsz) == 0 ? 1u : 0u;
+    table[i].grad = g;
+    table[i].decay = decay_mask ? decay_mask[i] : 1u;
+    table[i].vec_ok = g % (4 * gsz) == 0 ? 1u : 0u;
   }
-  static_assert(sizeof(GradSeg) == 16, "one entry a lane");
-  ++c->grad_seq;
-  LC_HIP(c, launch_fetch(c->dev_h_grad, c->d_grad, static_cast<uint32_t>(ns), &c->dev_h_state->grad_seq, c->grad_seq,
-                         c->stream));
+  if (fetched) {
+    static_assert(sizeof(GradSeg) == 16, "one entry a lane");
+    ++c->grad_seq;
+    LC_HIP(c, launch_fetch(c->dev_h_grad, c->d_grad, static_cast<uint32_t>(ns), &c->dev_h_state->grad_seq, c->grad_seq,
+                           c->stream));
+  }
   return LC_OK;
 }
 
@@ -981,7 +987,7 @@ lc_status lc_adamw_step_score(lc_ctx* c, int64_t step, const void* const* grads,
   sc.eps = static_cast<float>(p->eps);
   sc.lr = static_cast<float>(p->lr);
   sc.decay = static_cast<float>(1.0 - p->lr * p->weight_decay);
-  LC_HIP(c, launch_adamw(c->dt, grad_dtype, c->L.has_master ? 1 : 0, sc, c->stream));
+  LC_HIP(c, launch_adamw(c->dt, c->inline_grads, grad_dtype, c->L.has_master ? 1 : 0, sc, c->stream));
   return optimizer_end(c, step);
 }
 
@@ -999,7 +1005,7 @@ lc_status lc_sgd_step_score(lc_ctx* c, int64_t step, const void* const* grads, i
   SgdScalars sc;
   sc.lr = static_cast<float>(p->lr);
   sc.decay = static_cast<float>(1.0 - p->lr * p->weight_decay);
-  LC_HIP(c, launch_sgd(c->dt, grad_dtype, c->L.has_master ? 1 : 0, sc, c->stream));
+  LC_HIP(c, launch_sgd(c->dt, c->inline_grads, grad_dtype, c->L.has_master ? 1 : 0, sc, c->stream));
   return optimizer_end(c, step);
 }
 
