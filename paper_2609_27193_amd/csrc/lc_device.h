@@ -95,8 +95,14 @@ __device__ __forceinline__ uint32_t remap_xcd(uint32_t x, uint32_t G) {
 // items that are not alike (a W piece that is stored twice beside the other
 // pieces of a record), which contiguous eighths would leave to one XCD (one
 // 160 M element layer: SNAPSHOT pack 890 us in eighths, 726 us in runs of 64;
-// packs of several layers gain 0-4%; runs of 16 to 1024 are alike).  What is
-// left behind the last 8 full runs is shared out in contiguous eighths.
+// packs of several layers gain 0-4%; runs of 32 to 1024 are alike, of 16 lose
+// 4%, of 8 12%), and for chunks that are read and written, whose XCDs then work
+// in one window of HBM (us in eighths / runs of 8 / 16 / 32 / 256: ACCUM score
+// of 336 M bf16 weights 315 / 314 / 309 / 309 / 313, fp32 652 / 683 / 640 / 643;
+// AdamW, fp32 weights 1449 / 1435 / 1404 / 1389, bf16 with master 1556 / 1562 /
+// 1534 / 1551; SGD 642 / 636 / 632 / 635).  The SNAPSHOT score, which only
+// reads, keeps eighths (1.2 B weights: 693, in runs 698-708).  What is left
+// behind the last 8 full runs is shared out in contiguous eighths.
 template <uint32_t RUN>
 __device__ __forceinline__ uint32_t remap_xcd_runs(uint32_t x, uint32_t G) {
   constexpr uint32_t R = 8u * RUN;

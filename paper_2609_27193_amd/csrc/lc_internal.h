@@ -19,6 +19,9 @@ namespace lc {
 #ifndef LC_XCD_REMAP
 #define LC_XCD_REMAP 1
 #endif
+#ifndef LC_RW_XCD_RUN
+#define LC_RW_XCD_RUN 32  // consecutive chunks per XCD in the ACCUM score and the optimizer kernels
+#endif
 #ifndef LC_COPY_XCD_RUN
 #define LC_COPY_XCD_RUN 64  // consecutive pieces per XCD in the pack and unpack kernels
 #endif

@@ -180,7 +180,8 @@ __device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
 // range of chunks starting at chunk_base.
 template <int DT, bool ACCUM>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(const DeviceTables t, uint32_t chunk_base) {
-  score_chunk<DT, ACCUM>(t, chunk_base + remap_xcd(blockIdx.x, gridDim.x));
+  const uint32_t x = ACCUM ? remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, gridDim.x) : remap_xcd(blockIdx.x, gridDim.x);
+  score_chunk<DT, ACCUM>(t, chunk_base + x);
 }
 
 // ---- finalize: Eq. 1 and Eq. 2 per layer, one block per layer -----------------

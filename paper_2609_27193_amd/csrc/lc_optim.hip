@@ -303,7 +303,7 @@ template <int OPT, int WDT, int GDT, bool MASTER, bool LOOP, typename SC>
 __global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const DeviceTables t, const SC sc,
                                                                            const InlineGrads ig) {
   if constexpr (!LOOP) {
-    optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, remap_xcd(blockIdx.x, gridDim.x));
+    optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, gridDim.x));
   } else {
     for (uint64_t base = 0; base < t.n_chunks; base += gridDim.x) {
       const uint64_t left = t.n_chunks - base;
