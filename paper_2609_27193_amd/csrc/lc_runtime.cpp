@@ -257,14 +257,20 @@ lc_status check_ctx(lc_ctx* c) {
 // Wait for a number that a kernel of the stream writes into pinned host
 // memory.  The flag is polled, so the host reacts within a microsecond or two
 // of the kernel's store instead of after a device-to-host copy and a stream
-// synchronisation; every 256 polls the stream is queried, so an error ends the
-// wait, and so does a stream that drained without the number (`drained`).
+// synchronisation.  Now and then the stream is queried, so an error ends the
+// wait, and so does a stream that drained without the number (`drained`).  A
+// query takes microseconds and holds up the launch behind it, so there are
+// kPolls polls (about 50 us) between two: on 3.7 M parameters a decision step
+// takes 33.4 us and an AdamW step 42.7, with a query every 256 polls 36.6 and
+// 48.0.
+constexpr uint32_t kPolls = 1u << 16;
+
 hipError_t wait_number(lc_ctx* c, const uint64_t* number, uint64_t want, bool* drained) {
   const volatile uint64_t* flag = number;
   *drained = false;
   for (uint32_t spin = 1;; ++spin) {
     if (*flag == want) break;
-    if (spin % 256 == 0) {
+    if (spin % kPolls == 0) {
       const hipError_t q = hipStreamQuery(c->stream);
       if (q == hipSuccess) {
         *drained = *flag != want;
