@@ -193,14 +193,32 @@ struct SelectHeader {
 };
 static_assert(sizeof(SelectHeader) == 64, "header layout");
 
-// One rank of a restore: the layer, the address of its record, and the pieces
-// of the ranks before it (the entry behind the last holds their total).
+// One rank of a restore: the address of its record, the pieces of the ranks
+// before it (the entry behind the last holds their total), where its own
+// pieces begin in piece_unit, and the step that its record was persisted at.
 struct RankEntry {
   uint64_t src;
   uint64_t piece_prefix;
-  uint64_t layer;
-  uint64_t pad;
+  uint64_t piece_begin;
+  int64_t step;
 };
+
+// The ranks of a restore of every layer of a layout of few layers go into the
+// kernel's arguments, and the kernel sets Delta and t_l itself: one launch
+// instead of three and no table to fetch.
+constexpr uint32_t kInlineRanks = 108;
+struct UnpackArgs {
+  const uint32_t* piece_unit;
+  const CopyUnit* units;
+  const RankEntry* ranks;  // null: `inline_ranks`, which are every layer in order
+  double* delta;
+  int64_t* t_last;
+  uint64_t piece_base;     // first piece of this launch
+  uint32_t n_ranks;
+  uint32_t pad;
+  RankEntry inline_ranks[kInlineRanks + 1];
+};
+static_assert(sizeof(UnpackArgs) < 4096 - 256, "kernel arguments, with the launch's own");
 
 // Pinned host memory that small tables pass through, in both directions.
 // Followed by u, Delta and t_l of n_layers each (written by the device), then
@@ -260,7 +278,9 @@ hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, 
 hipError_t launch_pack(const DeviceTables& t, uint32_t first_rank, uint32_t last_rank,
                        uint64_t piece_base, uint64_t n_pieces, uint64_t rec_base,
                        void* staging, int refresh_shadow, hipStream_t st);
-hipError_t launch_unpack(const DeviceTables& t, uint32_t n_ranks, uint64_t n_pieces,
+// ranks (host, n_ranks + 1 entries): every layer, at most kInlineRanks, and
+// Delta and t_l are set, too; null: the ranks are in t.ranks.
+hipError_t launch_unpack(const DeviceTables& t, const RankEntry* ranks, uint32_t n_ranks, uint64_t n_pieces,
                          hipStream_t st);
 // Optimizer steps writing the per-chunk drift partials (lc_optim.hip).
 // t.grad_segs null: the gradient table is `grads`.

@@ -12,6 +12,7 @@
 //    the cross-wave combine.
 #include "lc_device.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace lc {
@@ -442,9 +443,9 @@ __device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint
     }
     done = nv * 16;
   }
-  const uint16_t* s2 = reinterpret_cast<const uint16_t*>(src);
-  uint16_t* d2 = reinterpret_cast<uint16_t*>(dst);
-  uint16_t* f2 = reinterpret_cast<uint16_t*>(dst2);
+  const g_u16* s2 = (const g_u16*)src;
+  g_u16* d2 = (g_u16*)dst;
+  g_u16* f2 = (g_u16*)dst2;
   for (uint32_t i = done / 2 + tid; i < len / 2; i += kCopyThreads) {
     const uint16_t x = s2[i];
     d2[i] = x;
@@ -476,7 +477,7 @@ __device__ __forceinline__ void pack_piece(const DeviceTables& t, uint32_t first
   copy_piece(src, dst, dst2, len);
   if (off + len == u.bytes) {  // zero the block's padding
     const uint32_t pad = static_cast<uint32_t>(round_up(u.bytes, kRecordAlign) - u.bytes);
-    uint16_t* z = reinterpret_cast<uint16_t*>(dst + len);
+    g_u16* z = (g_u16*)(dst + len);
     for (uint32_t i = threadIdx.x; i < pad / 2; i += kCopyThreads) z[i] = 0;
   }
 }
@@ -491,21 +492,21 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(const DeviceTables t
 }
 
 // ---- unpack: composite restore from device-resident records --------------------
-// rank r restores layer ranks[r].layer from the record at address ranks[r].src;
-// every W block also refreshes the shadow.  An array's pieces start behind its
-// head, on a line of the array, so that the stores do not split lines; the
-// array's first piece takes the head with it, and the last may be empty.
-__device__ __forceinline__ void unpack_piece(const DeviceTables& t, uint32_t n_ranks, uint64_t q) {
-  uint32_t lo = 0, hi = n_ranks;
+// rank r restores its layer from the record at address ranks[r].src; every W
+// block also refreshes the shadow.  An array's pieces start behind its head,
+// on a line of the array, so that the stores do not split lines; the array's
+// first piece takes the head with it, and the last may be empty.
+typedef __attribute__((address_space(4))) RankEntry c_RankEntry;
+
+__device__ __forceinline__ void unpack_piece(const UnpackArgs& t, const c_RankEntry* ranks, uint64_t q) {
+  uint32_t lo = 0, hi = t.n_ranks;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (t.ranks[mid].piece_prefix <= q) lo = mid; else hi = mid;
+    if (ranks[mid].piece_prefix <= q) lo = mid; else hi = mid;
   }
-  const RankEntry rank = t.ranks[lo];
-  const uint64_t l = rank.layer;
-  const uint64_t lp = q - rank.piece_prefix;
-  const CopyUnit u = t.units[t.piece_unit[t.layer_piece_begin[l] + lp]];
-  const uint8_t* src = reinterpret_cast<const uint8_t*>(rank.src) + u.rec_off;
+  const uint64_t lp = q - ranks[lo].piece_prefix;
+  const CopyUnit u = t.units[t.piece_unit[ranks[lo].piece_begin + lp]];
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(ranks[lo].src) + u.rec_off;
   uint8_t* dst = reinterpret_cast<uint8_t*>(u.arr);
   uint8_t* dst2 = u.shadow ? reinterpret_cast<uint8_t*>(u.shadow) : nullptr;
   const uint32_t p = static_cast<uint32_t>(lp) - u.piece0;
@@ -516,10 +517,19 @@ __device__ __forceinline__ void unpack_piece(const DeviceTables& t, uint32_t n_r
   if (len) copy_piece(src + off, dst + off, dst2 ? dst2 + off : nullptr, len);
 }
 
-// One piece per block, from piece_base on (split like the pack).
-__global__ __launch_bounds__(kCopyThreads) void unpack_kernel(const DeviceTables t, uint32_t n_ranks,
-                                                              uint64_t piece_base) {
-  unpack_piece(t, n_ranks, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, gridDim.x));
+// One piece per block, from piece_base on (split like the pack).  Ranks in the
+// arguments are read as the constants that the others are, too, and nothing is
+// stored before the tables are read: scalar loads (a store before them makes
+// the unit's lookup a vector load and costs 1.2% on 1.2 B parameters).
+__global__ __launch_bounds__(kCopyThreads) void unpack_kernel(const UnpackArgs t) {
+  const c_RankEntry* ranks = (const c_RankEntry*)(t.ranks ? t.ranks : t.inline_ranks);
+  unpack_piece(t, ranks, t.piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, gridDim.x));
+  if (!t.ranks && blockIdx.x == 0 && t.piece_base == 0) {
+    for (uint32_t l = threadIdx.x; l < t.n_ranks; l += kCopyThreads) {
+      t.delta[l] = 0.0;
+      t.t_last[l] = ranks[l].step;
+    }
+  }
 }
 
 // Each launch takes the largest grid one dispatch allows (grid_for) and the
@@ -635,11 +645,22 @@ hipError_t launch_pack(const DeviceTables& t, uint32_t first_rank, uint32_t last
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(const DeviceTables& t, uint32_t n_ranks, uint64_t n_pieces, hipStream_t st) {
+hipError_t launch_unpack(const DeviceTables& t, const RankEntry* ranks, uint32_t n_ranks, uint64_t n_pieces,
+                         hipStream_t st) {
+  UnpackArgs a;
+  a.piece_unit = t.piece_unit;
+  a.units = t.units;
+  a.ranks = ranks ? nullptr : t.ranks;
+  a.delta = t.delta;
+  a.t_last = t.t_last;
+  a.n_ranks = n_ranks;
+  a.pad = 0;
+  if (ranks) std::copy(ranks, ranks + n_ranks + 1, a.inline_ranks);
   const uint32_t lds = occupancy_lds(LC_COPY_BLOCKS_PER_CU);
   for (uint64_t done = 0; done < n_pieces;) {
     const uint32_t g = grid_for(n_pieces - done, kCopyThreads);
-    hipLaunchKernelGGL(unpack_kernel, dim3(g), dim3(kCopyThreads), lds, st, t, n_ranks, done);
+    a.piece_base = done;
+    hipLaunchKernelGGL(unpack_kernel, dim3(g), dim3(kCopyThreads), lds, st, a);
     done += g;
   }
   return hipGetLastError();

@@ -48,18 +48,18 @@ __device__ __forceinline__ float adamw_elem(float p, float& m, float& v, float g
 
 template <int WDT>
 __device__ __forceinline__ float w_load(const uint8_t* w, uint64_t i) {
-  if constexpr (WDT == 1) return __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(w)[i]) << 16);
-  else return reinterpret_cast<const float*>(w)[i];
+  if constexpr (WDT == 1) return __uint_as_float(static_cast<uint32_t>(((const g_u16*)w)[i]) << 16);
+  else return ((const g_f32*)w)[i];
 }
 template <int WDT>
 __device__ __forceinline__ void w_store(uint8_t* w, uint64_t i, float x) {
-  if constexpr (WDT == 1) reinterpret_cast<uint16_t*>(w)[i] = bf16_rne(x);
-  else reinterpret_cast<float*>(w)[i] = x;
+  if constexpr (WDT == 1) ((g_u16*)w)[i] = bf16_rne(x);
+  else ((g_f32*)w)[i] = x;
 }
 template <int GDT>
 __device__ __forceinline__ float g_load(const uint8_t* g, uint64_t i) {
-  if constexpr (GDT == 1) return __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(g)[i]) << 16);
-  else return reinterpret_cast<const float*>(g)[i];
+  if constexpr (GDT == 1) return __uint_as_float(static_cast<uint32_t>(((const g_u16*)g)[i]) << 16);
+  else return ((const g_f32*)g)[i];
 }
 
 // One SGD element update in fp32 with decoupled weight decay, one rounding
@@ -232,14 +232,14 @@ __device__ __forceinline__ void optim_tile(const ChunkPtrs& c, const SC& sc, boo
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
 __device__ __forceinline__ void optim_elem(const OptSeg& sg, const GradSeg& gs, const SC& sc, uint64_t e, double& a,
                                            double& b) {
-  const float po = MASTER ? reinterpret_cast<const float*>(sg.master)[e]
+  const float po = MASTER ? ((const g_f32*)sg.master)[e]
                           : w_load<WDT>(reinterpret_cast<const uint8_t*>(sg.w), e);
   const float gv = g_load<GDT>(reinterpret_cast<const uint8_t*>(gs.grad), e);
   const bool decay = gs.decay != 0;
   float x;
   if constexpr (OPT == kAdamW) {
-    float* mp = reinterpret_cast<float*>(sg.m) + e;
-    float* vp = reinterpret_cast<float*>(sg.v) + e;
+    g_f32* mp = (g_f32*)sg.m + e;
+    g_f32* vp = (g_f32*)sg.v + e;
     float mm = *mp, vv = *vp;
     x = adamw_elem(po, mm, vv, gv, sc, decay);
     *mp = mm;
@@ -247,7 +247,7 @@ __device__ __forceinline__ void optim_elem(const OptSeg& sg, const GradSeg& gs, 
   } else {
     x = sgd_elem(po, gv, sc, decay);
   }
-  if constexpr (MASTER) reinterpret_cast<float*>(sg.master)[e] = x;
+  if constexpr (MASTER) ((g_f32*)sg.master)[e] = x;
   w_store<WDT>(reinterpret_cast<uint8_t*>(sg.w), e, x);
   a += static_cast<double>(fabsf(x - po));
   b += static_cast<double>(fabsf(po));

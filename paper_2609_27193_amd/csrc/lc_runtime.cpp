@@ -462,10 +462,8 @@ lc_status restore_range_from_host(lc_ctx* c, uint32_t l, uint64_t rec_off, uint6
   return LC_OK;
 }
 
-lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& steps) {
-  std::memcpy(state_steps(c, c->h_state), steps.data(), c->L.N * sizeof(int64_t));
-  LC_HIP(c, launch_reset_state(c->dt, state_steps(c, c->dev_h_state), 0, c->stream));
-  LC_HIP(c, hipStreamSynchronize(c->stream));
+// The call-order state behind a restore.
+static void restore_done(lc_ctx* c, int64_t t_fail) {
   c->last_step = t_fail;
   c->scored = false;
   c->have_selection = false;
@@ -473,6 +471,13 @@ lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& 
   c->pending_persists = false;
   c->shadow_valid = c->L.has_shadow;
   c->result_on_host = false;
+}
+
+lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& steps) {
+  std::memcpy(state_steps(c, c->h_state), steps.data(), c->L.N * sizeof(int64_t));
+  LC_HIP(c, launch_reset_state(c->dt, state_steps(c, c->dev_h_state), 0, c->stream));
+  LC_HIP(c, hipStreamSynchronize(c->stream));
+  restore_done(c, t_fail);
   return LC_OK;
 }
 
@@ -853,19 +858,28 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
     for (uint32_t j = 0; j < l; ++j)
       if (v[i].mask[j]) off += L.rec_bytes[j];
     if (kind[i] == 0) {
-      ranks.push_back({reinterpret_cast<uint64_t>(dev_base[i] + off), pieces, l, 0});
+      ranks.push_back({reinterpret_cast<uint64_t>(dev_base[i] + off), pieces, L.layer_piece_begin[l], v[i].step});
       pieces += L.layer_pieces[l];
     } else {
       host_layers.emplace_back(l, static_cast<const uint8_t*>(v[i].payload) + off);
     }
   }
-  if (!ranks.empty()) {
-    const uint32_t n_ranks = static_cast<uint32_t>(ranks.size());
-    ranks.push_back({0, pieces, 0, 0});
+  std::vector<int64_t> steps(N);
+  for (uint32_t l = 0; l < N; ++l) steps[l] = v[choice[l]].step;
+  const uint32_t n_ranks = static_cast<uint32_t>(ranks.size());
+  ranks.push_back({0, pieces, 0, 0});
+  if (n_ranks == N && N <= kInlineRanks) {
+    LC_HIP(c, launch_unpack(c->dt, ranks.data(), n_ranks, pieces, c->stream));
+    LC_HIP(c, hipStreamSynchronize(c->stream));
+    restore_done(c, t_fail);
+    if (chosen_step_out) std::memcpy(chosen_step_out, steps.data(), N * sizeof(int64_t));
+    return LC_OK;
+  }
+  if (n_ranks) {
     std::memcpy(state_ranks(c, c->h_state), ranks.data(), ranks.size() * sizeof(RankEntry));
     LC_HIP(c, launch_fetch(state_ranks(c, c->dev_h_state), c->dt.ranks,
                            static_cast<uint32_t>(ranks.size() * (sizeof(RankEntry) / 16)), nullptr, 0, c->stream));
-    LC_HIP(c, launch_unpack(c->dt, n_ranks, pieces, c->stream));
+    LC_HIP(c, launch_unpack(c->dt, nullptr, n_ranks, pieces, c->stream));
   }
   StreamDrained drained{c, true};
   // host-resident records: one copy per block, then S <- W
@@ -873,8 +887,6 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
     st = restore_range_from_host(c, hl.first, 0, L.rec_bytes[hl.first], hl.second);
     if (st != LC_OK) return st;
   }
-  std::vector<int64_t> steps(N);
-  for (uint32_t l = 0; l < N; ++l) steps[l] = v[choice[l]].step;
   st = restore_finish(c, t_fail, steps);
   if (st != LC_OK) return st;
   drained.armed = false;

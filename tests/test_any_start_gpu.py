@@ -161,11 +161,11 @@ def test_segments_at_any_element(dtype, master, op, offsets):
         check("restore")
         # the same from host memory: page-locked (a kernel reads it), at odd places of one allocation, and pageable
         pinned = torch.empty(sum(h["payload"].nbytes + 256 for h in host), dtype=torch.uint8, pin_memory=True)
-        for where in ("pinned", "pageable"):
+        for where in ("pinned", "pageable", "mixed"):
             at, hv = 2, []
             for h in host:
                 k = h["payload"].nbytes
-                if where == "pinned":
+                if where == "pinned" or where == "mixed" and h["step"] == 1:
                     buf = pinned[at:at + k]
                     buf.copy_(torch.from_numpy(h["payload"].copy()))
                     at += k + 254
@@ -177,5 +177,53 @@ def test_segments_at_any_element(dtype, master, op, offsets):
                     d[a].buf[d[a].off:d[a].off + d[a].host.nbytes] = 0x33
             assert LC.lc_restore_composite(ctx, hv, 1, N).tolist() == chosen.tolist()
             check(f"restore from {where} memory")
+    finally:
+        LC.lc_destroy(ctx)
+
+
+@pytest.mark.parametrize("N", [1, 107, 108, 109, 300])
+def test_restore_of_any_number_of_layers(N):
+    """The ranks of a restore ride in the kernel's arguments up to 108 layers, beyond that in a table."""
+    import torch
+    sizes = [1 + l % 7 * 50 for l in range(N)]
+    arrs = [torch.arange(sum(sizes), device="cuda").float() + k for k in range(4)]  # w, s, m, v
+    segs, at = [], 0
+    for l, n in enumerate(sizes):
+        w, s, m, v = (a.data_ptr() + 4 * at for a in arrs)
+        segs.append(LC.Segment(l, n, w, s, None, m, v))
+        at += n
+    stream = torch.cuda.current_stream().cuda_stream
+    ctx = LC.lc_init_layout(LC.LayoutDesc(segs, N, LC.LC_DT_F32, False, LC.LC_MODE_ACCUM,
+                                          [0.0 if l % 3 == 0 else 1e300 for l in range(N)], s_max=99, stream=stream))
+    try:
+        total = sum(LC.lc_record_bytes(ctx, l) for l in range(N))
+        bufs, versions = [], []
+        for t in (0, 1):
+            if t:
+                for a in (arrs[0], arrs[2], arrs[3]):
+                    a += 0.5
+                LC.lc_score_layers(ctx, t)
+                mask, _ = LC.lc_select(ctx, t, 1.0, N)
+                assert mask.tolist() == [int(l % 3 == 0) for l in range(N)]
+            else:
+                mask = np.ones(N, np.uint8)
+            bufs.append(torch.empty(total, dtype=torch.uint8, device="cuda"))
+            r = LC.lc_pack_selected(ctx, bufs[t].data_ptr(), total, 0)
+            assert r["done"] == 1
+            versions.append({"step": t, "mask": mask, "payload": bufs[t].data_ptr(), "payload_bytes": r["bytes_written"]})
+        later = torch.repeat_interleave(torch.tensor([0.5 * (l % 3 == 0) for l in range(N)], device="cuda"),
+                                        torch.tensor(sizes, device="cuda"))
+        want = [torch.arange(sum(sizes), device="cuda").float() + k + later for k in range(4)]
+        for a in arrs:
+            a.fill_(-1.0)
+        assert LC.lc_restore_composite(ctx, versions, 3, N).tolist() == [int(l % 3 == 0) for l in range(N)]
+        for k in (0, 2, 3):
+            assert torch.equal(arrs[k], want[k]), k
+        assert torch.equal(arrs[1], want[0])
+        _, delta, t_last = LC.lc_read_state(ctx, N)
+        assert not delta.any() and t_last.tolist() == [int(l % 3 == 0) for l in range(N)]
+        with pytest.raises(LC.LCError):
+            LC.lc_score_layers(ctx, 3)  # the next step must exceed t_fail
+        LC.lc_score_layers(ctx, 4)
     finally:
         LC.lc_destroy(ctx)
