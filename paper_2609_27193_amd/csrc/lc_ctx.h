@@ -64,6 +64,7 @@ struct lc_ctx {
   double eps_w = 0;
   int64_t t_base = 0;
   hipStream_t stream = nullptr;
+  int device = 0;                    // current at init: the tables and the stream are its
   DeviceTables dt{};
   std::vector<void*> allocations;
   SelectHeader* h_result = nullptr;  // pinned, coherent: header + mask[N], written by the select kernel

@@ -220,6 +220,18 @@ lc_status dev_alloc(lc_ctx* c, T** p, size_t count) {
   return LC_OK;
 }
 
+// Calls that once made only copies, and so worked whatever device was current,
+// launch their kernels on the context's device.
+struct OnDevice {
+  int before = -1;
+  explicit OnDevice(const lc_ctx* c) {
+    if (hipGetDevice(&before) != hipSuccess || before == c->device || hipSetDevice(c->device) != hipSuccess) before = -1;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
 // Copies out of a caller's host payload must not outlive the call: an early
 // return (a failed call after some copies were enqueued) still waits for them.
 struct StreamDrained {
@@ -474,6 +486,7 @@ static void restore_done(lc_ctx* c, int64_t t_fail) {
 }
 
 lc_status restore_finish(lc_ctx* c, int64_t t_fail, const std::vector<int64_t>& steps) {
+  OnDevice on(c);
   std::memcpy(state_steps(c, c->h_state), steps.data(), c->L.N * sizeof(int64_t));
   LC_HIP(c, launch_reset_state(c->dt, state_steps(c, c->dev_h_state), 0, c->stream));
   LC_HIP(c, hipStreamSynchronize(c->stream));
@@ -576,6 +589,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   c->t_base = d->t_base;
   c->stream = static_cast<hipStream_t>(d->stream);
   c->last_step = d->t_base;
+  if (hipGetDevice(&c->device) != hipSuccess) (void)hipGetLastError();
   const HostLayout& L = c->L;
   const uint32_t N = L.N;
 
@@ -868,6 +882,7 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
   for (uint32_t l = 0; l < N; ++l) steps[l] = v[choice[l]].step;
   const uint32_t n_ranks = static_cast<uint32_t>(ranks.size());
   ranks.push_back({0, pieces, 0, 0});
+  OnDevice on(c);
   if (n_ranks == N && N <= kInlineRanks) {
     LC_HIP(c, launch_unpack(c->dt, ranks.data(), n_ranks, pieces, c->stream));
     LC_HIP(c, hipStreamSynchronize(c->stream));
@@ -1033,6 +1048,7 @@ lc_status lc_read_state(lc_ctx* c, double* u_out, double* delta_out, int64_t* t_
   if (st != LC_OK) return st;
   const size_t N = c->L.N;
   // a kernel behind all enqueued work writes the state into pinned memory
+  OnDevice on(c);
   ++c->state_seq;
   LC_HIP(c, launch_push_state(c->dt, c->dev_h_state, c->state_seq, c->stream));
   bool drained = false;
