@@ -203,10 +203,10 @@ __global__ __launch_bounds__(256) void tail_probe(const TailArgs g) {
     }
     if constexpr (REDUCE == 1) {
       lc::block_sum2<256>(a, b);
-      if (threadIdx.x == 0) g.partials[t] = make_double2(a, b);
+      if (threadIdx.x == 255) g.partials[t] = make_double2(a, b);
     } else {
-      lc::wave_sum2(a, b);
-      if ((threadIdx.x & 63) == 0) g.partials[t * 4 + (threadIdx.x >> 6)] = make_double2(a, b);
+      lc::wave_sum2<true>(a, b);
+      if ((threadIdx.x & 63) == 63) g.partials[t * 4 + (threadIdx.x >> 6)] = make_double2(a, b);
     }
   }
 }
