@@ -8,8 +8,12 @@
 //    Infinity Cache; full chunks and pieces go through buffer resources;
 //  * reductions use no floating-point atomics: one fp64 pair per chunk, then a
 //    fixed-order per-layer sum, so scores are bitwise reproducible;
-//  * wave64 reductions (DPP quad permutes, then cross-row shuffles), LDS for
-//    the cross-wave combine.
+//  * wave64 reductions (DPP moves or cross-row shuffles), LDS for the
+//    cross-wave combine;
+//  * kernels take the few tables that they read as arguments of their own, not
+//    the struct of all of them: the loads of the arguments stand together and
+//    wait once.  On 3.7 M parameters, where trips to memory bound every kernel,
+//    the decision step takes 28.8 us, with the struct 30.0.
 #include "lc_device.h"
 
 #include <algorithm>
@@ -150,10 +154,11 @@ __device__ __forceinline__ void score_tile(const uint8_t* wb, uint8_t* sb, uint3
 // Streams W and S of one chunk once; writes (sum|W-S|, sum|S|) in fp64.  In
 // ACCUM mode the same pass stores W into S (the next step's W(t-1)).
 template <int DT, bool ACCUM>
-__device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
+__device__ __forceinline__ void score_chunk(const ScoreSeg* segs, const uint32_t* chunk_seg, double2* partials,
+                                            uint32_t c) {
   constexpr uint32_t ESZ = DT == 1 ? 2 : 4;
   constexpr uint32_t CE = kChunkBytes / ESZ;  // elements per chunk
-  const ScoreSeg sg = t.segs[t.chunk_seg[c]];
+  const ScoreSeg sg = segs[chunk_seg[c]];
   const uint32_t k = c - sg.chunk_begin;
   const uint64_t e0 = static_cast<uint64_t>(k) * CE + sg.head;  // the chunk's tile
   const uint64_t rem = sg.numel > e0 ? sg.numel - e0 : 0;
@@ -172,7 +177,7 @@ __device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
     if constexpr (ACCUM) elem_copy<DT>(w, s, threadIdx.x);
   }
   block_sum2<kScoreThreads, ACCUM>(a, b);
-  if (threadIdx.x == kScoreThreads - 1) t.partials[c] = make_double2(a, b);
+  if (threadIdx.x == kScoreThreads - 1) partials[c] = make_double2(a, b);
 }
 
 // One chunk per block: the chunk's tables are read before any store, so they
@@ -180,9 +185,11 @@ __device__ __forceinline__ void score_chunk(const DeviceTables& t, uint32_t c) {
 // (2^32 work-items) is scored by consecutive launches, each over the next
 // range of chunks starting at chunk_base.
 template <int DT, bool ACCUM>
-__global__ __launch_bounds__(kScoreThreads) void score_kernel(const DeviceTables t, uint32_t chunk_base) {
-  const uint32_t x = ACCUM ? remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, gridDim.x) : remap_xcd(blockIdx.x, gridDim.x);
-  score_chunk<DT, ACCUM>(t, chunk_base + x);
+__global__ __launch_bounds__(kScoreThreads) void score_kernel(const ScoreSeg* segs, const uint32_t* chunk_seg,
+                                                              double2* partials, uint32_t chunk_base,
+                                                              uint32_t blocks) {
+  const uint32_t x = ACCUM ? remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, blocks) : remap_xcd(blockIdx.x, blocks);
+  score_chunk<DT, ACCUM>(segs, chunk_seg, partials, chunk_base + x);
 }
 
 // ---- finalize: Eq. 1 and Eq. 2 per layer, one block per layer -----------------
@@ -193,17 +200,20 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const DeviceTables
 // does not depend on the partials is loaded first (3.7 M parameters: decision
 // step 29.7 -> 28.9 us); of a large layer, the load rate of its one CU does
 // (64 K partials 12 us).
-__global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const DeviceTables t) {
+__global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const uint32_t* layer_chunk_begin,
+                                                                    const double2* partials, const uint64_t* numel_of,
+                                                                    double* delta_of, double* u_of, double eps_w,
+                                                                    int mode) {
   const uint32_t l = blockIdx.x;
-  const uint32_t c0 = t.layer_chunk_begin[l], c1 = t.layer_chunk_begin[l + 1];
-  const uint64_t numel = t.numel[l];
-  const double delta = t.delta[l], eps_w = t.eps_w;
+  const uint32_t c0 = layer_chunk_begin[l], c1 = layer_chunk_begin[l + 1];
+  const uint64_t numel = numel_of[l];
+  const double delta = delta_of[l];
   double a[4] = {0.0, 0.0, 0.0, 0.0}, b[4] = {0.0, 0.0, 0.0, 0.0};
   uint32_t c = c0 + threadIdx.x;
   for (; c + 3 * kFinalizeThreads < c1; c += 4 * kFinalizeThreads) {
     double2 p[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) p[k] = t.partials[c + k * kFinalizeThreads];
+    for (int k = 0; k < 4; ++k) p[k] = partials[c + k * kFinalizeThreads];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       a[k] += p[k].x;
@@ -214,7 +224,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const Device
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     if (c < c1) {
-      const double2 p = t.partials[c];
+      const double2 p = partials[c];
       a[k] += p.x;
       b[k] += p.y;
       c += kFinalizeThreads;
@@ -226,8 +236,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const Device
   if (threadIdx.x == kFinalizeThreads - 1) {
     const double n = static_cast<double>(numel);
     const double u = (x / n) / (y / n + eps_w);
-    t.u[l] = u;
-    t.delta[l] = (t.mode == 0) ? delta + u : u;
+    u_of[l] = u;
+    delta_of[l] = (mode == 0) ? delta + u : u;
   }
 }
 
@@ -267,11 +277,13 @@ struct SelectSums {
 // bounds it.  On 18-35 layers behind a score that has swept the caches it
 // takes 5 us, where one lane that walked the layers took 8-11.
 template <uint32_t NT>
-__global__ __launch_bounds__(NT) void select_kernel(const DeviceTables t, int64_t step, double lr_scale, int base_mode,
-                                                    uint64_t seq) {
+__global__ __launch_bounds__(NT) void select_kernel(const uint64_t* numel, const uint64_t* rec_bytes,
+                                                    const uint64_t* layer_pieces, int64_t* t_last, const double* k0,
+                                                    double* delta, uint32_t n_layers, int base_mode, DeviceTables t,
+                                                    int64_t step, double lr_scale, uint64_t seq) {
   constexpr uint32_t NW = NT / 64;
   __shared__ SelectSums wave_total[NW];
-  const uint32_t N = t.n_layers, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t N = n_layers, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   SelectHeader* hr = t.host_result;
   uint8_t* mask = reinterpret_cast<uint8_t*>(hr + 1);
   SelectSums before{};  // of the rounds before this one
@@ -280,16 +292,16 @@ __global__ __launch_bounds__(NT) void select_kernel(const DeviceTables t, int64_
     SelectSums s{};
     if (l < N) {
       uint32_t code = 1;  // bit0 selected, bit1 selected by the staleness guard alone
-      const uint64_t n = t.numel[l], rec = t.rec_bytes[l], pieces = t.layer_pieces[l];
-      int64_t age = step - t.t_last[l];
+      const uint64_t n = numel[l], rec = rec_bytes[l], pieces = layer_pieces[l];
+      int64_t age = step - t_last[l];
       if (!base_mode) {
-        const double K = t.k0[l] * lr_scale;
-        const bool by_drift = t.delta[l] >= K;
+        const double K = k0[l] * lr_scale;
+        const bool by_drift = delta[l] >= K;
         const bool by_age = age >= t.s_max;
         code = ((by_drift || by_age) ? 1u : 0u) | ((!by_drift && by_age) ? 2u : 0u);
         if (code & 1u) {
-          t.delta[l] = 0.0;
-          t.t_last[l] = step;
+          delta[l] = 0.0;
+          t_last[l] = step;
           age = 0;
         }
       }
@@ -457,8 +469,17 @@ __device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint
 // Work item q is piece q (relative to piece_base) of the selected records of
 // ranks [first, last); records are written from staging offset
 // sel_rec_prefix[first] - rec_base.
+struct PackTables {
+  const uint64_t* sel_piece_prefix;
+  const uint32_t* sel_layer;
+  const uint64_t* layer_piece_begin;
+  const uint32_t* piece_unit;
+  const CopyUnit* units;
+  const uint64_t* sel_rec_prefix;
+};
+
 template <bool REFRESH>
-__device__ __forceinline__ void pack_piece(const DeviceTables& t, uint32_t first, uint32_t last, uint64_t q,
+__device__ __forceinline__ void pack_piece(const PackTables& t, uint32_t first, uint32_t last, uint64_t q,
                                            uint64_t rec_base, uint8_t* staging) {
   uint32_t lo = first, hi = last;  // sel_piece_prefix[lo] <= q < sel_piece_prefix[hi]
   while (hi - lo > 1) {
@@ -485,10 +506,16 @@ __device__ __forceinline__ void pack_piece(const DeviceTables& t, uint32_t first
 // One piece per block; piece_base is the first piece of this launch (a pack
 // with more pieces than one dispatch takes is split into consecutive launches).
 template <bool REFRESH>
-__global__ __launch_bounds__(kCopyThreads) void pack_kernel(const DeviceTables t, uint32_t first,
-                                                            uint32_t last, uint64_t piece_base,
-                                                            uint64_t rec_base, uint8_t* staging) {
-  pack_piece<REFRESH>(t, first, last, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, gridDim.x), rec_base, staging);
+__global__ __launch_bounds__(kCopyThreads) void pack_kernel(const uint64_t* sel_piece_prefix,
+                                                            const uint32_t* sel_layer,
+                                                            const uint64_t* layer_piece_begin,
+                                                            const uint32_t* piece_unit, const CopyUnit* units,
+                                                            uint64_t piece_base, uint32_t first, uint32_t last,
+                                                            uint32_t blocks,
+                                                            const uint64_t* sel_rec_prefix, uint64_t rec_base,
+                                                            uint8_t* staging) {
+  const PackTables t{sel_piece_prefix, sel_layer, layer_piece_begin, piece_unit, units, sel_rec_prefix};
+  pack_piece<REFRESH>(t, first, last, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, blocks), rec_base, staging);
 }
 
 // ---- unpack: composite restore from device-resident records --------------------
@@ -544,8 +571,8 @@ void launch_score_t(const DeviceTables& t, hipStream_t st) {
                        : occupancy_lds(ACCUM ? LC_SCORE_ACCUM_BLOCKS_PER_CU : LC_SCORE_SNAPSHOT_BLOCKS_PER_CU);
   for (uint64_t done = 0; done < t.n_chunks;) {
     const uint32_t g = grid_for(t.n_chunks - done, kScoreThreads);
-    hipLaunchKernelGGL((score_kernel<DT, ACCUM>), dim3(g), dim3(kScoreThreads), lds, st, t,
-                       static_cast<uint32_t>(done));
+    hipLaunchKernelGGL((score_kernel<DT, ACCUM>), dim3(g), dim3(kScoreThreads), lds, st, t.segs,
+                       t.chunk_seg, t.partials, static_cast<uint32_t>(done), g);
     done += g;
   }
 }
@@ -556,8 +583,9 @@ void launch_pack_t(const DeviceTables& t, uint32_t first, uint32_t last, uint64_
   const uint32_t lds = occupancy_lds(LC_COPY_BLOCKS_PER_CU);
   for (uint64_t done = 0; done < n_pieces;) {
     const uint32_t g = grid_for(n_pieces - done, kCopyThreads);
-    hipLaunchKernelGGL((pack_kernel<REFRESH>), dim3(g), dim3(kCopyThreads), lds, st, t, first, last,
-                       piece_base + done, rec_base, stg);
+    hipLaunchKernelGGL((pack_kernel<REFRESH>), dim3(g), dim3(kCopyThreads), lds, st, t.sel_piece_prefix, t.sel_layer,
+                       t.layer_piece_begin, t.piece_unit, t.units, piece_base + done, first, last, g,
+                       t.sel_rec_prefix, rec_base, stg);
     done += g;
   }
 }
@@ -601,22 +629,23 @@ hipError_t launch_score(const DeviceTables& t, hipStream_t st) {
     if (t.mode == 0) launch_score_t<2, true>(t, st);
     else launch_score_t<2, false>(t, st);
   }
-  hipLaunchKernelGGL(finalize_kernel, dim3(t.n_layers), dim3(kFinalizeThreads), 0, st, t);
-  return hipGetLastError();
+  return launch_finalize(t, st);
 }
 
 hipError_t launch_finalize(const DeviceTables& t, hipStream_t st) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(t.n_layers), dim3(kFinalizeThreads), 0, st, t);
+  hipLaunchKernelGGL(finalize_kernel, dim3(t.n_layers), dim3(kFinalizeThreads), 0, st, t.layer_chunk_begin, t.partials,
+                     t.numel, t.delta, t.u, t.eps_w, t.mode);
   return hipGetLastError();
 }
 
 hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, int base_mode, uint64_t seq,
                          hipStream_t st) {
   if (t.n_layers <= 64)
-    hipLaunchKernelGGL(select_kernel<64>, dim3(1), dim3(64), 0, st, t, step, lr_scale, base_mode, seq);
+    hipLaunchKernelGGL(select_kernel<64>, dim3(1), dim3(64), 0, st, t.numel, t.rec_bytes, t.layer_pieces, t.t_last,
+                       t.k0, t.delta, t.n_layers, base_mode, t, step, lr_scale, seq);
   else
-    hipLaunchKernelGGL(select_kernel<kSelectThreads>, dim3(1), dim3(kSelectThreads), 0, st, t, step, lr_scale, base_mode,
-                       seq);
+    hipLaunchKernelGGL(select_kernel<kSelectThreads>, dim3(1), dim3(kSelectThreads), 0, st, t.numel, t.rec_bytes,
+                       t.layer_pieces, t.t_last, t.k0, t.delta, t.n_layers, base_mode, t, step, lr_scale, seq);
   return hipGetLastError();
 }
 

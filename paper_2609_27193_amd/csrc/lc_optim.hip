@@ -255,8 +255,15 @@ __device__ __forceinline__ void optim_elem(const OptSeg& sg, const GradSeg& gs, 
 
 typedef __attribute__((address_space(4))) GradSeg c_GradSeg;
 
+struct OptTables {
+  const uint32_t* chunk_seg;
+  const OptSeg* opt_segs;
+  const GradSeg* grad_segs;
+  double2* partials;
+};
+
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
-__device__ __forceinline__ void optim_chunk(const DeviceTables& t, const InlineGrads& ig, const SC& sc, uint32_t c) {
+__device__ __forceinline__ void optim_chunk(const OptTables& t, const InlineGrads& ig, const SC& sc, uint32_t c) {
   constexpr uint32_t WSZ = WDT == 1 ? 2 : 4, GSZ = GDT == 1 ? 2 : 4;
   constexpr uint32_t CE = kChunkBytes / WSZ;  // elements per chunk (the score chunks)
   const uint32_t tid = threadIdx.x;
@@ -300,14 +307,16 @@ __device__ __forceinline__ void optim_chunk(const DeviceTables& t, const InlineG
 }
 
 template <int OPT, int WDT, int GDT, bool MASTER, bool LOOP, typename SC>
-__global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(const DeviceTables t, const SC sc,
-                                                                           const InlineGrads ig) {
+__global__ __launch_bounds__((kOptThreads<WDT, MASTER>)) void optim_kernel(
+    const uint32_t* chunk_seg, const OptSeg* opt_segs, const GradSeg* grad_segs, double2* partials, uint32_t n_chunks,
+    uint32_t blocks, const SC sc, const InlineGrads ig) {
+  const OptTables t{chunk_seg, opt_segs, grad_segs, partials};
   if constexpr (!LOOP) {
-    optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, gridDim.x));
+    optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, blocks));
   } else {
-    for (uint64_t base = 0; base < t.n_chunks; base += gridDim.x) {
-      const uint64_t left = t.n_chunks - base;
-      const uint32_t span = left < gridDim.x ? static_cast<uint32_t>(left) : gridDim.x;
+    for (uint64_t base = 0; base < n_chunks; base += blocks) {
+      const uint64_t left = n_chunks - base;
+      const uint32_t span = left < blocks ? static_cast<uint32_t>(left) : blocks;
       if (blockIdx.x >= span) return;
       optim_chunk<OPT, WDT, GDT, MASTER>(t, ig, sc, static_cast<uint32_t>(base + remap_xcd(blockIdx.x, span)));
       __syncthreads();
@@ -340,9 +349,11 @@ void launch_optim_t(const DeviceTables& t, const InlineGrads& ig, const SC& sc, 
                               : tile >= kOptBytesPerCU ? 1 : fit < 2 ? 2 : fit;
   const uint32_t lds = occupancy_lds(blocks);
   if (g == t.n_chunks)
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc, ig);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, false, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds,
+                       st, t.chunk_seg, t.opt_segs, t.grad_segs, t.partials, t.n_chunks, g, sc, ig);
   else
-    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds, st, t, sc, ig);
+    hipLaunchKernelGGL((optim_kernel<OPT, WDT, GDT, MASTER, true, SC>), dim3(g), dim3(kOptThreads<WDT, MASTER>), lds,
+                       st, t.chunk_seg, t.opt_segs, t.grad_segs, t.partials, t.n_chunks, g, sc, ig);
 }
 
 template <int OPT, typename SC>
