@@ -518,7 +518,7 @@ __global__ __launch_bounds__(kCopyThreads) void pack_kernel(const uint64_t* sel_
   pack_piece<REFRESH>(t, first, last, piece_base + remap_xcd_runs<LC_COPY_XCD_RUN>(blockIdx.x, blocks), rec_base, staging);
 }
 
-// ---- unpack: composite restore from device-resident records --------------------
+// ---- unpack: composite restore from records in device or pinned host memory ----
 // rank r restores its layer from the record at address ranks[r].src; every W
 // block also refreshes the shadow.  An array's pieces start behind its head,
 // on a line of the array, so that the stores do not split lines; the array's
