@@ -1,6 +1,7 @@
 """GPU: every chunk and piece of a launch is worked on exactly once, whatever
 the number of blocks leaves behind the last runs of the block -> item mapping
-(runs of 32 chunks and of 64 pieces per XCD, 8 XCDs)."""
+(runs of 32 chunks and of 64 pieces per XCD, 8 XCDs; ACCUM scores of more than
+9 * 2^18 chunks in runs of 512)."""
 import pytest
 
 from paper_2609_27193_amd import layercheck as LC
@@ -55,5 +56,33 @@ def test_each_item_once(chunks):
         assert LC.lc_restore_composite(ctx, versions, 1, 1).tolist() == [1]
         assert torch.equal(W, (idx % 1021).float() + 1.0) and torch.equal(S, W)
         assert torch.equal(m, (idx % 1019).float()) and torch.equal(v, (idx % 1013).float())
+    finally:
+        LC.lc_destroy(ctx)
+
+
+@pytest.mark.parametrize("past", [0, 1, 4096 - (9 << 18) % 4096 + 8])
+def test_each_chunk_once_on_a_large_state(past):
+    import torch
+    n = ((9 << 18) + past) * (LC.lc_query_build()["chunk_bytes"] // 2) - 3
+    if torch.cuda.mem_get_info()[0] < 5 * n:
+        pytest.skip("needs 48 GB of device memory")
+    dev, stream = torch.device("cuda"), torch.cuda.current_stream().cuda_stream
+    base = (torch.arange(251 << 16, device=dev) % 251).bfloat16()  # integers below 2^8: exact, also one more
+    W = torch.empty(n, dtype=torch.bfloat16, device=dev)
+    total = 0.0
+    for i in range(0, n, base.numel()):
+        part = base[:min(base.numel(), n - i)]
+        W[i:i + part.numel()] = part
+        total += float(part.double().sum())
+    S = torch.zeros_like(W)
+    seg = LC.Segment(0, n, W.data_ptr(), S.data_ptr(), None, None, None)
+    ctx = LC.lc_init_layout(LC.LayoutDesc([seg], 1, LC.LC_DT_BF16, False, LC.LC_MODE_ACCUM, [0.0], s_max=9, stream=stream))
+    try:
+        W += 1.0
+        LC.lc_score_layers(ctx, 1)
+        u = LC.lc_read_state(ctx, 1)[0][0]
+        want = 1.0 / (total / n + 1e-8)
+        assert abs(u - want) <= 1e-12 * want, (u, want)  # a chunk left out or taken twice is 4e-7 of it
+        assert torch.equal(S, W)
     finally:
         LC.lc_destroy(ctx)
