@@ -935,8 +935,8 @@ lc_status lc_rebase(lc_ctx* c, int64_t step) {
 namespace {
 
 // Shared by the optimizer steps: validation of the call and the gradient
-// table, its upload, and the call-order state afterwards (the caller
-// launches its kernel between the two halves).
+// table, its way to the device, and the call-order state afterwards (the
+// caller launches its kernel between the two halves).
 lc_status optimizer_begin(lc_ctx* c, int64_t step, const void* const* grads, int32_t grad_dtype,
                           const uint8_t* decay_mask) {
   if (!grads) return fail(LC_ERR_INVALID_ARG, "grads must be non-NULL");
