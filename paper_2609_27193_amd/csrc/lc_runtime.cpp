@@ -232,8 +232,9 @@ struct OnDevice {
   }
 };
 
-// Copies out of a caller's host payload must not outlive the call: an early
-// return (a failed call after some copies were enqueued) still waits for them.
+// What reads a caller's payload must not outlive the call: an early return (a
+// failed launch or copy behind some that were enqueued) still waits for them.
+// Stands before the first of them.
 struct StreamDrained {
   lc_ctx* c;
   bool armed;
@@ -883,9 +884,11 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
   const uint32_t n_ranks = static_cast<uint32_t>(ranks.size());
   ranks.push_back({0, pieces, 0, 0});
   OnDevice on(c);
+  StreamDrained drained{c, true};
   if (n_ranks == N && N <= kInlineRanks) {
     LC_HIP(c, launch_unpack(c->dt, ranks.data(), n_ranks, pieces, c->stream));
     LC_HIP(c, hipStreamSynchronize(c->stream));
+    drained.armed = false;
     restore_done(c, t_fail);
     if (chosen_step_out) std::memcpy(chosen_step_out, steps.data(), N * sizeof(int64_t));
     return LC_OK;
@@ -896,7 +899,6 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
                            static_cast<uint32_t>(ranks.size() * (sizeof(RankEntry) / 16)), nullptr, 0, c->stream));
     LC_HIP(c, launch_unpack(c->dt, nullptr, n_ranks, pieces, c->stream));
   }
-  StreamDrained drained{c, true};
   // host-resident records: one copy per block, then S <- W
   for (const auto& hl : host_layers) {
     st = restore_range_from_host(c, hl.first, 0, L.rec_bytes[hl.first], hl.second);

@@ -1,0 +1,92 @@
+"""What the library's host code asks of HIP, and in which order, without a
+GPU: a child process runs a scenario on a preloaded stand-in for the HIP host
+calls (tests/hip_standin.c), which runs no kernel and writes the calls down."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from paper_2609_27193_amd.build_lib import GRID_CAPPED_LIB, LIB
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+DEVICE, HOST = 2, 1  # hipMemoryTypeDevice, hipMemoryTypeHost
+
+
+@pytest.fixture(scope="module")
+def standin(tmp_path_factory):
+    gcc, rocm = shutil.which("gcc"), os.environ.get("ROCM_PATH", "/opt/rocm")
+    if not gcc or not os.path.exists(LIB) or not os.path.exists(GRID_CAPPED_LIB):
+        pytest.skip("needs gcc and the libraries of __graft_entry__.build()")
+    so = str(tmp_path_factory.mktemp("standin") / "libhip_standin.so")
+    subprocess.run([gcc, "-std=c11", "-O1", "-Wall", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(rocm, "include"), os.path.join(ROOT, "tests", "hip_standin.c"),
+                    "-o", so], check=True)
+    return so
+
+
+def in_child(standin, lib, scenario, *args):
+    env = dict(os.environ, LD_PRELOAD=standin, HIP_STANDIN=standin, LAYERCHECK_LIB=lib)
+    r = subprocess.run([sys.executable, "-c", f"import tests.test_host_calls as t; t.{scenario}(*{args!r})"],
+                       cwd=ROOT, env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+
+
+# ---- in the child: no torch, nothing touches a GPU --------------------------------------------------------------------
+
+
+def hip():
+    h = C.CDLL(os.environ["HIP_STANDIN"])
+    h.standin_log.restype = C.c_char_p
+    h.standin_alloc.restype = C.c_void_p
+    h.standin_alloc.argtypes = [C.c_size_t, C.c_int]
+    h.words = lambda: [w.split(":")[0] for w in h.standin_log().decode().split()]
+    return h
+
+
+def context(h, sizes):
+    """One fp32 segment a layer, weights, shadow and moments."""
+    from paper_2609_27193_amd import layercheck as LC
+    segs = [LC.Segment(l, n, *(h.standin_alloc(4 * n, DEVICE) for _ in "ws"), None,
+                       *(h.standin_alloc(4 * n, DEVICE) for _ in "mv")) for l, n in enumerate(sizes)]
+    ctx = LC.lc_init_layout(LC.LayoutDesc(segs, len(sizes), LC.LC_DT_F32, False, LC.LC_MODE_ACCUM, [1.0] * len(sizes), 9))
+    h.standin_clear()
+    return LC, ctx
+
+
+def failed_restore(n_layers, where):
+    import numpy as np
+    h = hip()
+    sizes = [40 * 2048] * 3 + [1] * (n_layers - 3)
+    LC, ctx = context(h, sizes)
+    total = sum(LC.lc_record_bytes(ctx, l) for l in range(n_layers))
+    v = [{"step": 0, "mask": np.ones(n_layers, np.uint8), "payload": h.standin_alloc(total, where), "payload_bytes": total}]
+    launches = 0
+    for fail in range(1, 1000):  # every launch of the call fails once
+        h.standin_clear()
+        h.standin_fail_launch(fail)
+        try:
+            LC.lc_restore_composite(ctx, v, 0, n_layers)
+        except LC.LCError as e:
+            assert e.code == LC.LC_ERR_HIP
+            w = h.words()
+            # an earlier launch may still read the payload and write the arrays
+            assert w[-1] == "sync", (fail, w)
+            launches = fail
+            _, ctx = context(h, sizes)  # the failed one is out of use
+            continue
+        break
+    assert launches >= 3, launches
+
+
+# ---- the tests ---------------------------------------------------------------------------------------------------------
+
+
+@pytest.mark.parametrize("where", [DEVICE, HOST], ids=["device", "page-locked"])
+@pytest.mark.parametrize("n_layers", [3, 108, 109])
+def test_a_failed_restore_waits_for_what_it_launched(standin, n_layers, where):
+    """The caller may free or reuse the payload as soon as the call has returned, also with an error; the ranks ride in
+    the kernel's arguments up to 108 layers, beyond that in a table."""
+    in_child(standin, GRID_CAPPED_LIB, "failed_restore", n_layers, where)
