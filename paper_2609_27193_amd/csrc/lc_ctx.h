@@ -71,7 +71,6 @@ struct lc_ctx {
   uint64_t result_seq = 0;           // sequence number of the last select kernel enqueued
   HostState* h_state = nullptr;      // pinned, coherent: numbers, per-layer state, restore tables
   HostState* dev_h_state = nullptr;  // its device address
-  uint64_t state_seq = 0;            // sequence number of the last state read enqueued
   lc::InlineGrads inline_grads{};    // per-call gradient table of a layout of few segments
   GradSeg* h_grad = nullptr;         // else: pinned, coherent
   GradSeg* dev_h_grad = nullptr;     // its device address

@@ -222,13 +222,11 @@ static_assert(sizeof(UnpackArgs) < 4096 - 256, "kernel arguments, with the launc
 
 // Pinned host memory that small tables pass through, in both directions.
 // Followed by u, Delta and t_l of n_layers each (written by the device), then
-// n_layers + 1 RankEntry and n_layers steps of a restore (written by the host).  The numbers
-// are written last by the device: state_seq when the state is there, grad_seq
-// when the gradient table has been read.
+// n_layers + 1 RankEntry and n_layers steps of a restore (written by the host).
+// grad_seq is written by the device when the gradient table has been read.
 struct HostState {
-  uint64_t state_seq;
   uint64_t grad_seq;
-  uint64_t reserved[6];
+  uint64_t reserved[7];
 };
 static_assert(sizeof(HostState) == 64, "tables stay 16-byte aligned");
 
@@ -273,7 +271,7 @@ hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, i
                          hipStream_t st);
 // Small tables through pinned host memory (HostState): device addresses.
 hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st);
-hipError_t launch_push_state(const DeviceTables& t, HostState* host, uint64_t seq, hipStream_t st);
+hipError_t launch_push_state(const DeviceTables& t, HostState* host, hipStream_t st);
 hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, int64_t step, hipStream_t st);
 hipError_t launch_pack(const DeviceTables& t, uint32_t first_rank, uint32_t last_rank,
                        uint64_t piece_base, uint64_t n_pieces, uint64_t rec_base,

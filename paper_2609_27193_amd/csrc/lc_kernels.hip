@@ -384,9 +384,8 @@ __global__ __launch_bounds__(kTableThreads) void fetch_kernel(const u32x4* src, 
   if (threadIdx.x == 0 && flag) *reinterpret_cast<volatile uint64_t*>(flag) = seq;
 }
 
-// u, Delta and t_l of every layer to pinned host memory, then the number the
-// host waits for.
-__global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceTables t, HostState* h, uint64_t seq) {
+// u, Delta and t_l of every layer to pinned host memory.
+__global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceTables t, HostState* h) {
   const uint32_t N = t.n_layers;
   double* u = reinterpret_cast<double*>(h + 1);
   for (uint32_t l = threadIdx.x; l < N; l += kTableThreads) {
@@ -394,9 +393,6 @@ __global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceT
     u[N + l] = t.delta[l];
     reinterpret_cast<int64_t*>(u)[2 * N + l] = t.t_last[l];
   }
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) *reinterpret_cast<volatile uint64_t*>(&h->state_seq) = seq;
 }
 
 // Delta = 0 and t_l = steps[l] (or one step for all) of every layer.
@@ -669,8 +665,8 @@ hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t*
   return hipGetLastError();
 }
 
-hipError_t launch_push_state(const DeviceTables& t, HostState* host, uint64_t seq, hipStream_t st) {
-  hipLaunchKernelGGL(push_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host, seq);
+hipError_t launch_push_state(const DeviceTables& t, HostState* host, hipStream_t st) {
+  hipLaunchKernelGGL(push_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host);
   return hipGetLastError();
 }
 

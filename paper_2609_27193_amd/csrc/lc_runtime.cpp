@@ -1049,16 +1049,13 @@ lc_status lc_read_state(lc_ctx* c, double* u_out, double* delta_out, int64_t* t_
   lc_status st = check_ctx(c);
   if (st != LC_OK) return st;
   const size_t N = c->L.N;
-  // a kernel behind all enqueued work writes the state into pinned memory
+  // A kernel behind all enqueued work writes the state into pinned memory.  The
+  // call synchronises the stream, as it promises: 18.2 us on 200 layers, three
+  // copies of the runtime behind a synchronisation 51; a number polled in its
+  // place 13.8, but then the stream may still be busy.
   OnDevice on(c);
-  ++c->state_seq;
-  LC_HIP(c, launch_push_state(c->dt, c->dev_h_state, c->state_seq, c->stream));
-  bool drained = false;
-  LC_HIP(c, wait_number(c, &c->h_state->state_seq, c->state_seq, &drained));
-  if (drained) {
-    c->poisoned = true;
-    return fail(LC_ERR_HIP, "the state never reached the host");
-  }
+  LC_HIP(c, launch_push_state(c->dt, c->dev_h_state, c->stream));
+  LC_HIP(c, hipStreamSynchronize(c->stream));
   const double* h = reinterpret_cast<const double*>(c->h_state + 1);
   if (u_out) std::memcpy(u_out, h, N * sizeof(double));
   if (delta_out) std::memcpy(delta_out, h + N, N * sizeof(double));

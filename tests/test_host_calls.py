@@ -81,6 +81,15 @@ def failed_restore(n_layers, where):
     assert launches >= 3, launches
 
 
+def state_read():
+    h = hip()
+    LC, ctx = context(h, [5, 3000, 1])
+    LC.lc_score_layers(ctx, 1)
+    assert h.words()[-1] != "sync"
+    LC.lc_read_state(ctx, 3)
+    assert h.words()[-1] == "sync", h.words()
+
+
 # ---- the tests ---------------------------------------------------------------------------------------------------------
 
 
@@ -90,3 +99,8 @@ def test_a_failed_restore_waits_for_what_it_launched(standin, n_layers, where):
     """The caller may free or reuse the payload as soon as the call has returned, also with an error; the ranks ride in
     the kernel's arguments up to 108 layers, beyond that in a table."""
     in_child(standin, GRID_CAPPED_LIB, "failed_restore", n_layers, where)
+
+
+def test_reading_the_state_synchronises_the_stream(standin):
+    """As the header promises: the stream is idle when the call returns."""
+    in_child(standin, LIB, "state_read")
