@@ -43,6 +43,7 @@ constexpr uint32_t kRecordAlign = 256u;
 constexpr uint32_t kFinalizeThreads = 1024;
 constexpr uint32_t kSelectThreads = 256;  // beyond 64 layers
 constexpr uint32_t kTableThreads = 256;
+constexpr uint32_t kTableBlocks = 32;  // at most
 
 // Resident blocks per CU of the streaming kernels (0: as many as registers
 // and waves allow), held there by a dynamic LDS reservation the kernel never

@@ -371,9 +371,9 @@ __global__ __launch_bounds__(NT) void select_kernel(const uint64_t* numel, const
 }
 
 // ---- small tables between pinned host memory and the device ---------------------
-// One block each, beside the streaming kernels in the same stream: a copy
-// command of the runtime waits for its own engine or kernel and leaves gaps
-// of 6-20 us around it, and a copy back to the host a round trip each.
+// Beside the streaming kernels in the same stream: a copy command of the
+// runtime waits for its own engine or kernel and leaves gaps of 6-20 us around
+// it, and a copy back to the host a round trip each.
 
 // n 16-byte entries from pinned host memory; the flag tells the host that the
 // source may be written again.
@@ -384,11 +384,15 @@ __global__ __launch_bounds__(kTableThreads) void fetch_kernel(const u32x4* src, 
   if (threadIdx.x == 0 && flag) *reinterpret_cast<volatile uint64_t*>(flag) = seq;
 }
 
-// u, Delta and t_l of every layer to pinned host memory.
+// u, Delta and t_l of every layer to pinned host memory, an entry of each a
+// thread up to kTableBlocks blocks: trips over the host link bound it (whole
+// call, us, one block / 32 / 128: 1024 layers 18.1 / 17.4 / 17.4, 8192 34.0 /
+// 25.5 / 25.6, 20000 59.0 / 38.6 / 38.6, 100000 265 / 145 / 145; three copies of
+// the runtime 49.8, 37.8, 62.8, 156).
 __global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceTables t, HostState* h) {
   const uint32_t N = t.n_layers;
   double* u = reinterpret_cast<double*>(h + 1);
-  for (uint32_t l = threadIdx.x; l < N; l += kTableThreads) {
+  for (uint32_t l = blockIdx.x * kTableThreads + threadIdx.x; l < N; l += gridDim.x * kTableThreads) {
     u[l] = t.u[l];
     u[N + l] = t.delta[l];
     reinterpret_cast<int64_t*>(u)[2 * N + l] = t.t_last[l];
@@ -659,6 +663,8 @@ hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, i
   return hipGetLastError();
 }
 
+static uint32_t table_blocks(uint32_t n) { return std::min(kTableBlocks, (n + kTableThreads - 1) / kTableThreads); }
+
 hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st) {
   hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kTableThreads), 0, st, static_cast<const u32x4*>(host_src),
                      static_cast<u32x4*>(dst), n16, flag, seq);
@@ -666,7 +672,7 @@ hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t*
 }
 
 hipError_t launch_push_state(const DeviceTables& t, HostState* host, hipStream_t st) {
-  hipLaunchKernelGGL(push_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host);
+  hipLaunchKernelGGL(push_state_kernel, dim3(table_blocks(t.n_layers)), dim3(kTableThreads), 0, st, t, host);
   return hipGetLastError();
 }
 
