@@ -375,11 +375,11 @@ __global__ __launch_bounds__(NT) void select_kernel(const uint64_t* numel, const
 // runtime waits for its own engine or kernel and leaves gaps of 6-20 us around
 // it, and a copy back to the host a round trip each.
 
-// n 16-byte entries from pinned host memory; the flag tells the host that the
-// source may be written again.
+// n 16-byte entries from pinned host memory; the flag, which needs a launch of
+// one block, tells the host that the source may be written again.
 __global__ __launch_bounds__(kTableThreads) void fetch_kernel(const u32x4* src, u32x4* dst, uint32_t n, uint64_t* flag,
                                                               uint64_t seq) {
-  for (uint32_t i = threadIdx.x; i < n; i += kTableThreads) dst[i] = src[i];
+  for (uint32_t i = blockIdx.x * kTableThreads + threadIdx.x; i < n; i += gridDim.x * kTableThreads) dst[i] = src[i];
   __syncthreads();  // every load has returned: its value was stored
   if (threadIdx.x == 0 && flag) *reinterpret_cast<volatile uint64_t*>(flag) = seq;
 }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kTableThreads) void push_state_kernel(const DeviceT
 // Delta = 0 and t_l = steps[l] (or one step for all) of every layer.
 __global__ __launch_bounds__(kTableThreads) void reset_state_kernel(const DeviceTables t, const int64_t* steps,
                                                                     int64_t step) {
-  for (uint32_t l = threadIdx.x; l < t.n_layers; l += kTableThreads) {
+  for (uint32_t l = blockIdx.x * kTableThreads + threadIdx.x; l < t.n_layers; l += gridDim.x * kTableThreads) {
     t.delta[l] = 0.0;
     t.t_last[l] = steps ? steps[l] : step;
   }
@@ -665,9 +665,19 @@ hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, i
 
 static uint32_t table_blocks(uint32_t n) { return std::min(kTableBlocks, (n + kTableThreads - 1) / kTableThreads); }
 
+// Beyond kOneBlockEntries the entries are shared out to several blocks and the
+// flag is set by a launch behind them, which costs 2 us and more than that is
+// saved (an SGD step of n segments as a C call, us, one block / several; a copy
+// command of the runtime): 600: 14.6 / 16.1, 15.5; 1500: 20.2 / 17.2, 31; 5000:
+// 53.7 / 34.8, 49; 20000: 186 / 103, 127; 100000: 941 / 524, 571.
+constexpr uint32_t kOneBlockEntries = 1024;
+
 hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st) {
-  hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kTableThreads), 0, st, static_cast<const u32x4*>(host_src),
-                     static_cast<u32x4*>(dst), n16, flag, seq);
+  const bool one = flag && n16 <= kOneBlockEntries;
+  hipLaunchKernelGGL(fetch_kernel, dim3(one ? 1 : table_blocks(n16)), dim3(kTableThreads), 0, st,
+                     static_cast<const u32x4*>(host_src), static_cast<u32x4*>(dst), n16, one ? flag : nullptr, seq);
+  if (flag && !one)
+    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kTableThreads), 0, st, nullptr, nullptr, 0, flag, seq);
   return hipGetLastError();
 }
 
@@ -677,7 +687,7 @@ hipError_t launch_push_state(const DeviceTables& t, HostState* host, hipStream_t
 }
 
 hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, int64_t step, hipStream_t st) {
-  hipLaunchKernelGGL(reset_state_kernel, dim3(1), dim3(kTableThreads), 0, st, t, host_steps, step);
+  hipLaunchKernelGGL(reset_state_kernel, dim3(table_blocks(t.n_layers)), dim3(kTableThreads), 0, st, t, host_steps, step);
   return hipGetLastError();
 }
 

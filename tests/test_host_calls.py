@@ -90,6 +90,20 @@ def state_read():
     assert h.words()[-1] == "sync", h.words()
 
 
+def gradient_tables(n, fetches):
+    h = hip()
+    LC, ctx = context(h, [1] * n)
+    g = [h.standin_alloc(4, DEVICE)] * n
+    LC.lc_sgd_step_score(ctx, 1, g, LC.LC_DT_F32, 1e-3, 0.0)
+    first = [w for w in h.words() if "fetch_kernel" in w or w == "query"]
+    assert len(first) == fetches and "query" not in first, first  # nothing to wait for yet
+    h.standin_clear()
+    h.standin_busy(3)  # the fetch has not run: the number it writes is not there, and the stream is busy
+    LC.lc_sgd_step_score(ctx, 2, g, LC.LC_DT_F32, 1e-3, 0.0)
+    w = [x for x in h.words() if "fetch_kernel" in x or x == "query"]
+    assert w == ["query"] * (4 if fetches else 0) + first, w
+
+
 # ---- the tests ---------------------------------------------------------------------------------------------------------
 
 
@@ -104,3 +118,10 @@ def test_a_failed_restore_waits_for_what_it_launched(standin, n_layers, where):
 def test_reading_the_state_synchronises_the_stream(standin):
     """As the header promises: the stream is idle when the call returns."""
     in_child(standin, LIB, "state_read")
+
+
+@pytest.mark.parametrize("n,fetches", [(224, 0), (225, 1), (1024, 1), (1025, 2)])
+def test_a_gradient_table_waits_for_the_fetch_of_the_one_before(standin, n, fetches):
+    """Up to 224 segments the table rides in the kernel's arguments; beyond that the page-locked table may not be written
+    while the fetch of the previous call is under way (beyond 1024 a second launch behind the fetch says that it is done)."""
+    in_child(standin, LIB, "gradient_tables", n, fetches)

@@ -44,3 +44,51 @@ def test_state_of_every_layer(n):
         assert np.array_equal(t_last, np.where(l % 3, 0, 5))
     finally:
         LC.lc_destroy(ctx)
+
+
+@pytest.mark.parametrize("opt", ["sgd", "adamw"])
+@pytest.mark.parametrize("n", [223, 224, 225, 300, 1024, 1025, 8193])
+def test_gradient_tables_back_to_back(n, opt):
+    """The gradients' addresses ride in the kernel's arguments up to 224 segments, beyond that in a page-locked table that
+    one block or, beyond 1024 segments, several fetch.  The steps follow each other with no read between them, behind a
+    stream that is still busy, each with other gradients and other decayed segments: a table that the next call writes too
+    early, or that is not read whole, shows in the parameters."""
+    import torch
+    steps, lr, wd, f = 6, 2.0 ** -4, 2.0, np.float32
+    w, m, v = torch.full((n,), 64.0, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    rng = np.random.default_rng(n)
+    stream = torch.cuda.current_stream().cuda_stream
+    grads = [torch.from_numpy(rng.integers(-8, 8, n).astype(np.float32)).cuda() for _ in range(steps)]
+    order = [rng.permutation(n) for _ in range(steps)]  # segment l takes the gradient at order[l]
+    decay = [rng.integers(0, 2, n).astype(np.uint8) for _ in range(steps)]
+    ptrs = [[g.data_ptr() + 4 * int(k) for k in o] for g, o in zip(grads, order)]
+    want = np.full(n, 64.0, np.float32)
+    ref_m, ref_v = np.zeros(n, np.float32), np.zeros(n, np.float32)
+    ctx = LC.lc_init_layout(LC.LayoutDesc(tiny_layers(n, w=w, m=m, v=v), n, LC.LC_DT_F32, False, LC.LC_MODE_ACCUM,
+                                          [1e300] * n, s_max=99, stream=stream))
+    try:
+        torch.cuda.synchronize()
+        busy = torch.zeros(256 << 20, dtype=torch.uint8, device="cuda")
+        for _ in range(8):
+            busy += 1
+        for t in range(steps):
+            if opt == "sgd":
+                LC.lc_sgd_step_score(ctx, t + 1, ptrs[t], LC.LC_DT_F32, lr, wd, decay[t])
+            else:
+                LC.lc_adamw_step_score(ctx, t + 1, ptrs[t], LC.LC_DT_F32, lr, 0.5, 0.5, 1e-8, wd, t + 1, decay[t])
+        host = [x.cpu().numpy() for x in grads]
+        for t in range(steps):
+            g = host[t][order[t]]
+            d = np.where(decay[t] == 1, want * f(1.0 - lr * wd), want)
+            if opt == "sgd":
+                want = d - f(lr) * g
+            else:
+                ref_m = f(0.5) * ref_m + f(0.5) * g
+                ref_v = f(0.5) * ref_v + f(0.5) * (g * g)
+                c = f(1.0 / (1.0 - 0.5 ** (t + 1)))
+                want = d - f(lr) * ((ref_m * c) / (np.sqrt(ref_v * c) + f(1e-8)))
+        assert np.array_equal(w.cpu().numpy(), want.astype(np.float32))
+        if opt == "adamw":
+            assert np.array_equal(m.cpu().numpy(), ref_m) and np.array_equal(v.cpu().numpy(), ref_v)
+    finally:
+        LC.lc_destroy(ctx)
