@@ -228,6 +228,15 @@ __device__ __forceinline__ void optim_tile(const ChunkPtrs& c, const SC& sc, boo
   }
 }
 
+// Whether a gradient apart from state arrays that are aligned at element 0
+// leaves these their tiles (ANYG).  160 M elements, gradient at an odd element,
+// every array through unaligned accesses / only the gradient, AdamW and SGD
+// (us): bf16 with master, bf16 gradients 793 / 724 and 308 / 305, fp32 gradients
+// 802 / 768 and 358 / 349; bf16 alone 561 / 551 and 153 / 153; fp32 with bf16
+// gradients 698 / 683 and 252 / 252, with fp32 gradients 734 / 737 and 312 / 319.
+template <int WDT, int GDT, bool MASTER>
+constexpr bool kGradApart = MASTER || WDT == 1 || GDT == 1;
+
 // Element e of a segment.
 template <int OPT, int WDT, int GDT, bool MASTER, typename SC>
 __device__ __forceinline__ void optim_elem(const OptSeg& sg, const GradSeg& gs, const SC& sc, uint64_t e, double& a,
@@ -287,7 +296,7 @@ __device__ __forceinline__ void optim_chunk(const OptTables& t, const InlineGrad
   double a = 0.0, b = 0.0;
   if (n == CE && pairs) {
     optim_tile<OPT, WDT, GDT, MASTER, false, false, false>(cp, sc, decay, a, b);
-  } else if (n == CE && sg.form == kOptWide) {
+  } else if (n == CE && (sg.form == kOptWide || (kGradApart<WDT, GDT, MASTER> && sg.form == kOptPairs))) {
     optim_tile<OPT, WDT, GDT, MASTER, true, true, false>(cp, sc, decay, a, b);
   } else if (n == CE) {
     optim_tile<OPT, WDT, GDT, MASTER, true, true, true>(cp, sc, decay, a, b);

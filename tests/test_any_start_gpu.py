@@ -61,9 +61,10 @@ def lengths(esz):
 # element offsets of (weights, shadow, fp32 arrays, gradient), taken in turn by the segments
 ALIKE = [(e, e, e, e) for e in (1, 7, 8, 33, 0)]
 APART = [(1, 0, 0, 2), (0, 1, 3, 1), (5, 2, 1, 0), (0, 0, 1, 3), (8, 16, 4, 8), (3, 3, 0, 3), (0, 8, 0, 0)]
+GRAD = [(0, 0, 0, 1), (0, 0, 0, 2), (0, 1, 0, 3), (8, 8, 8, 7), (0, 0, 0, 0)]  # the gradient alone
 
 
-@pytest.mark.parametrize("offsets", [ALIKE, APART], ids=["alike", "apart"])
+@pytest.mark.parametrize("offsets", [ALIKE, APART, GRAD], ids=["alike", "apart", "gradient"])
 @pytest.mark.parametrize("dtype,master,op", [("bf16", True, "accum"), ("bf16", False, "snapshot"), ("f32", False, "accum"),
                                              ("f32", True, "snapshot"), ("bf16", True, "adamw"), ("bf16", False, "adamw"),
                                              ("f32", False, "adamw"), ("bf16", True, "sgd"), ("f32", False, "sgd")])
