@@ -180,24 +180,15 @@ __device__ __forceinline__ void score_chunk(const ScoreSeg* segs, const uint32_t
   if (threadIdx.x == kScoreThreads - 1) partials[c] = make_double2(a, b);
 }
 
-// Launches of more chunks than this (18 GiB of weights) deal them to the XCDs in
-// longer runs: ACCUM, bf16, runs of 32 / 512, means of five processes (us): 4.9 B
-// weights 4611 / 4665, 8.0 B 7424 / 7457, 9.8 B 9088 / 9033, 11.7 B 10999 / 10936,
-// 14.8 B 13689 / 13586.  Kernels of their own: the choice inside one costs 0.3%.
-constexpr uint32_t kLongRunBlocks = 9u << 18;
-constexpr uint32_t kLongRun = 512;
-
 // One chunk per block: the chunk's tables are read before any store, so they
 // stay on the scalar path.  A layout with more chunks than one dispatch takes
 // (2^32 work-items) is scored by consecutive launches, each over the next
-// range of chunks starting at chunk_base.  RUN 0: in eighths.
-template <int DT, bool ACCUM, uint32_t RUN>
+// range of chunks starting at chunk_base.
+template <int DT, bool ACCUM>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(const ScoreSeg* segs, const uint32_t* chunk_seg,
                                                               double2* partials, uint32_t chunk_base,
                                                               uint32_t blocks) {
-  uint32_t x;
-  if constexpr (RUN != 0) x = remap_xcd_runs<RUN>(blockIdx.x, blocks);
-  else x = remap_xcd(blockIdx.x, blocks);
+  const uint32_t x = ACCUM ? remap_xcd_runs<LC_RW_XCD_RUN>(blockIdx.x, blocks) : remap_xcd(blockIdx.x, blocks);
   score_chunk<DT, ACCUM>(segs, chunk_seg, partials, chunk_base + x);
 }
 
@@ -580,13 +571,8 @@ void launch_score_t(const DeviceTables& t, hipStream_t st) {
                        : occupancy_lds(ACCUM ? LC_SCORE_ACCUM_BLOCKS_PER_CU : LC_SCORE_SNAPSHOT_BLOCKS_PER_CU);
   for (uint64_t done = 0; done < t.n_chunks;) {
     const uint32_t g = grid_for(t.n_chunks - done, kScoreThreads);
-    constexpr uint32_t kRun = ACCUM ? LC_RW_XCD_RUN : 0, kLong = ACCUM ? kLongRun : 0;
-    if (g > kLongRunBlocks)
-      hipLaunchKernelGGL((score_kernel<DT, ACCUM, kLong>), dim3(g), dim3(kScoreThreads), lds, st,
-                         t.segs, t.chunk_seg, t.partials, static_cast<uint32_t>(done), g);
-    else
-      hipLaunchKernelGGL((score_kernel<DT, ACCUM, kRun>), dim3(g), dim3(kScoreThreads), lds, st,
-                         t.segs, t.chunk_seg, t.partials, static_cast<uint32_t>(done), g);
+    hipLaunchKernelGGL((score_kernel<DT, ACCUM>), dim3(g), dim3(kScoreThreads), lds, st, t.segs,
+                       t.chunk_seg, t.partials, static_cast<uint32_t>(done), g);
     done += g;
   }
 }

@@ -1,7 +1,6 @@
 """GPU: every chunk and piece of a launch is worked on exactly once, whatever
 the number of blocks leaves behind the last runs of the block -> item mapping
-(runs of 32 chunks and of 64 pieces per XCD, 8 XCDs; ACCUM scores of more than
-9 * 2^18 chunks in runs of 512)."""
+(runs of 32 chunks and of 64 pieces per XCD, 8 XCDs), also on a large state."""
 import pytest
 
 from paper_2609_27193_amd import layercheck as LC
