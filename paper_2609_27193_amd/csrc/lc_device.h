@@ -105,11 +105,16 @@ __device__ __forceinline__ uint32_t remap_xcd(uint32_t x, uint32_t G) {
 // behind the last 8 full runs is shared out in contiguous eighths.
 template <uint32_t RUN>
 __device__ __forceinline__ uint32_t remap_xcd_runs(uint32_t x, uint32_t G) {
+#if LC_XCD_REMAP
   constexpr uint32_t R = 8u * RUN;
   const uint32_t full = G - G % R;
   if (x >= full) return full + remap_xcd(x - full, G - full);
   const uint32_t k = x / 8u;
   return (k / RUN) * R + x % 8u * RUN + k % RUN;
+#else
+  (void)G;
+  return x;
+#endif
 }
 
 // ---- wave64 / block reductions of an fp64 pair, fixed order ------------------

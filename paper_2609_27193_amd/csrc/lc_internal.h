@@ -17,7 +17,7 @@ namespace lc {
 #define LC_CHUNK_BYTES (8u * 1024u)
 #endif
 #ifndef LC_XCD_REMAP
-#define LC_XCD_REMAP 1
+#define LC_XCD_REMAP 1  // 0: blocks take their items as they are dispatched (tuning builds)
 #endif
 #ifndef LC_RW_XCD_RUN
 #define LC_RW_XCD_RUN 32  // consecutive chunks per XCD in the ACCUM score and the optimizer kernels
