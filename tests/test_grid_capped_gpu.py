@@ -3,9 +3,9 @@ block up to the 2^32 work-item dispatch limit; beyond it the score and copy
 kernels are launched again over the next range of items and the optimizer
 kernels loop.  The parity tests rarely reach the limit, so a build with
 every grid capped at 40 blocks (`__graft_entry__.build()` makes it) runs the
-parity, edge and optimizer tests again in a child process: the score and
-copy kernels then run as many consecutive launches, the optimizer kernels
-over many rounds."""
+parity, edge, optimizer and any-element tests again in a child process: the
+score and copy kernels then run as many consecutive launches, the optimizer
+kernels over many rounds."""
 import os
 import subprocess
 import sys
@@ -27,6 +27,7 @@ def test_parity_with_capped_grids():
     r = subprocess.run([sys.executable, "-u", "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider", "-m", "gpu",
                         "--timeout", "300", "--timeout-method", "thread",
                         "tests/test_parity_gpu.py", "tests/test_edges_gpu.py", "tests/test_adamw_gpu.py",
+                        "tests/test_any_start_gpu.py",
                         "-k", "not 4gib and not many_layers"],
                        cwd=ROOT, env=env, capture_output=True, text=True, timeout=900)
     tail = (r.stdout + r.stderr)[-3000:]
