@@ -263,7 +263,8 @@ struct DeviceTables {
   RankEntry* ranks;                   // [N+1] restore scratch
 };
 
-// Launchers: return hipGetLastError() of the launches.
+// Launchers: return hipGetLastError() of the launches; the fetch, the state's
+// kernels and the unpack their own launches' error only.
 // launch_score: score kernel, then the finalize kernel (u and Delta).
 hipError_t launch_score(const DeviceTables& t, hipStream_t st);
 // Eq. 1-2 from the per-chunk partials alone (after an optimizer step).

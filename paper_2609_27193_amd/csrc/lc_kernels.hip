@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 namespace lc {
 namespace {
@@ -649,6 +650,18 @@ hipError_t launch_select(const DeviceTables& t, int64_t step, double lr_scale, i
   return hipGetLastError();
 }
 
+// A launch that reports its own error and leaves the caller's alone: for the
+// kernels that stand in a copy's place, in calls that a stale error of the
+// program has never failed.
+template <typename... P>
+static hipError_t launch_own(void (*kernel)(P...), uint32_t grid, uint32_t threads, uint32_t lds, hipStream_t st,
+                             std::common_type_t<P>... args) {
+  void* at[] = {&args...};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(grid), dim3(threads), at, lds, st);
+  if (e != hipSuccess) (void)hipGetLastError();  // reported here
+  return e;
+}
+
 static uint32_t table_blocks(uint32_t n) { return std::min(kTableBlocks, (n + kTableThreads - 1) / kTableThreads); }
 
 // Beyond kOneBlockEntries the entries are shared out to several blocks and the
@@ -660,21 +673,19 @@ constexpr uint32_t kOneBlockEntries = 1024;
 
 hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st) {
   const bool one = flag && n16 <= kOneBlockEntries;
-  hipLaunchKernelGGL(fetch_kernel, dim3(one ? 1 : table_blocks(n16)), dim3(kTableThreads), 0, st,
-                     static_cast<const u32x4*>(host_src), static_cast<u32x4*>(dst), n16, one ? flag : nullptr, seq);
-  if (flag && !one)
-    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kTableThreads), 0, st, nullptr, nullptr, 0, flag, seq);
-  return hipGetLastError();
+  const hipError_t e = launch_own(fetch_kernel, one ? 1 : table_blocks(n16), kTableThreads, 0, st,
+                                  static_cast<const u32x4*>(host_src), static_cast<u32x4*>(dst), n16,
+                                  one ? flag : nullptr, seq);
+  if (e != hipSuccess || !flag || one) return e;
+  return launch_own(fetch_kernel, 1, kTableThreads, 0, st, nullptr, nullptr, 0, flag, seq);
 }
 
 hipError_t launch_push_state(const DeviceTables& t, HostState* host, hipStream_t st) {
-  hipLaunchKernelGGL(push_state_kernel, dim3(table_blocks(t.n_layers)), dim3(kTableThreads), 0, st, t, host);
-  return hipGetLastError();
+  return launch_own(push_state_kernel, table_blocks(t.n_layers), kTableThreads, 0, st, t, host);
 }
 
 hipError_t launch_reset_state(const DeviceTables& t, const int64_t* host_steps, int64_t step, hipStream_t st) {
-  hipLaunchKernelGGL(reset_state_kernel, dim3(table_blocks(t.n_layers)), dim3(kTableThreads), 0, st, t, host_steps, step);
-  return hipGetLastError();
+  return launch_own(reset_state_kernel, table_blocks(t.n_layers), kTableThreads, 0, st, t, host_steps, step);
 }
 
 hipError_t launch_pack(const DeviceTables& t, uint32_t first_rank, uint32_t last_rank,
@@ -701,10 +712,11 @@ hipError_t launch_unpack(const DeviceTables& t, const RankEntry* ranks, uint32_t
   for (uint64_t done = 0; done < n_pieces;) {
     const uint32_t g = grid_for(n_pieces - done, kCopyThreads);
     a.piece_base = done;
-    hipLaunchKernelGGL(unpack_kernel, dim3(g), dim3(kCopyThreads), lds, st, a);
+    const hipError_t e = launch_own(unpack_kernel, g, kCopyThreads, lds, st, a);
+    if (e != hipSuccess) return e;
     done += g;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace lc

@@ -31,6 +31,7 @@ const char *standin_log(void) { return log_text; }
 void standin_clear(void) { log_len = 0; log_text[0] = 0; }
 void standin_fail_launch(int n) { fail_launch = n; }   /* the n-th launch from now on; 0: none */
 void standin_busy(int n) { busy_queries = n; }         /* so many queries say "not ready" */
+void standin_stale_error(void) { last_error = hipErrorOutOfMemory; } /* as an earlier call of the program leaves it */
 void *standin_alloc(size_t bytes, int type) {
   void *p = aligned_alloc(256, (bytes + 255) / 256 * 256);
   if (!p || n_ranges == MAX_RANGES) abort();

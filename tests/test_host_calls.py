@@ -90,6 +90,20 @@ def state_read():
     assert h.words()[-1] == "sync", h.words()
 
 
+def stale_error(where, n_layers):
+    import numpy as np
+    h = hip()
+    LC, ctx = context(h, [3000] * n_layers)
+    total = sum(LC.lc_record_bytes(ctx, l) for l in range(n_layers))
+    pageable = (C.c_uint8 * total)()
+    at = h.standin_alloc(total, where) if where else C.addressof(pageable)
+    v = [{"step": 0, "mask": np.ones(n_layers, np.uint8), "payload": at, "payload_bytes": total}]
+    h.standin_stale_error()
+    LC.lc_read_state(ctx, n_layers)
+    h.standin_stale_error()
+    LC.lc_restore_composite(ctx, v, 0, n_layers)
+
+
 def gradient_tables(n, fetches):
     h = hip()
     LC, ctx = context(h, [1] * n)
@@ -132,6 +146,14 @@ def test_a_failed_restore_waits_for_what_it_launched(standin, n_layers, where):
 def test_reading_the_state_synchronises_the_stream(standin):
     """As the header promises: the stream is idle when the call returns."""
     in_child(standin, LIB, "state_read")
+
+
+@pytest.mark.parametrize("where", [HOST, 0], ids=["page-locked", "pageable"])
+@pytest.mark.parametrize("n_layers", [3, 109])
+def test_an_error_of_the_program_fails_no_state_read_or_restore(standin, n_layers, where):
+    """A call of the program that failed before leaves its error with the runtime.  The state read and the restore from
+    host memory ask for their own launches' errors only, as copies do."""
+    in_child(standin, LIB, "stale_error", where, n_layers)
 
 
 @pytest.mark.parametrize("n,fetches", [(224, 0), (225, 1), (1024, 1), (1025, 2)])
