@@ -48,10 +48,6 @@ struct HostLayout {
   std::vector<uint32_t> piece_unit;
   std::vector<uint64_t> layer_piece_begin;  // [N+1]
   uint64_t total_numel = 0;
-
-  uint32_t layer_blocks(uint32_t l) const {  // blocks of the layer's record: one per array and segment
-    return (layer_seg_begin[l + 1] - layer_seg_begin[l]) * (1u + (has_master ? 1u : 0u) + (has_moments ? 2u : 0u));
-  }
 };
 
 }  // namespace lc

@@ -440,13 +440,6 @@ bool DeviceRanges::ok(const void* p, uint64_t bytes) {
   return true;
 }
 
-// Layers whose page-locked records have blocks of this size in the mean, or
-// larger ones, are copied block by block: the copy engine moves 57 GB/s, the kernel 55.6, which
-// from here on outweighs the 13 us that a copy costs beside its transfer (fp32
-// blocks of 12 / 40 / 80 / 160 MB, ms, kernel / copies: 8.43 / 8.74, 8.65 /
-// 8.61, 8.66 / 8.53, 8.66 / 8.49).
-static constexpr uint64_t kPinnedCopyBlock = 32ull << 20;
-
 // Whether a kernel can read [p, p + bytes): all of it in one allocation of
 // page-locked host memory that the device sees at the same address, as far as
 // HIP can tell.
@@ -464,9 +457,10 @@ static bool pinned_range_ok(const void* p, uint64_t bytes, const hipPointerAttri
 
 lc_status restore_range_from_host(lc_ctx* c, uint32_t l, uint64_t rec_off, uint64_t len, const uint8_t* bytes) {
   const HostLayout& L = c->L;
+  const uint32_t per_seg = 1u + (L.has_master ? 1u : 0u) + (L.has_moments ? 2u : 0u);
   uint32_t ub = 0;
-  for (uint32_t j = 0; j < l; ++j) ub += L.layer_blocks(j);
-  const uint32_t nu = L.layer_blocks(l);
+  for (uint32_t j = 0; j < l; ++j) ub += (L.layer_seg_begin[j + 1] - L.layer_seg_begin[j]) * per_seg;
+  const uint32_t nu = (L.layer_seg_begin[l + 1] - L.layer_seg_begin[l]) * per_seg;
   const uint64_t end = rec_off + len;
   for (uint32_t k = 0; k < nu; ++k) {
     const CopyUnit& u = L.units[ub + k];
@@ -849,12 +843,7 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
     choice[l] = best;
   }
   // record address of each layer, and where each version's payload lives
-  // 0 device memory, read by the unpack kernel; 1 pageable host memory, copied;
-  // 2 page-locked host memory: the unpack kernel reads the layers of blocks below
-  // kPinnedCopyBlock over the host link, one launch for any number of blocks,
-  // where a copy command per block and shadow takes turns with the link (67 M
-  // parameters in 111 tensors 20.9 -> 16.8 ms)
-  std::vector<int> kind(n_versions, -1);
+  std::vector<int> kind(n_versions, -1);  // 0 read by the unpack kernel, 1 copied (pageable host memory)
   std::vector<const uint8_t*> dev_base(n_versions, nullptr);
   std::vector<RankEntry> ranks;
   uint64_t pieces = 0;
@@ -870,7 +859,13 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
         kind[i] = 0;
         dev_base[i] = static_cast<const uint8_t*>(v[i].payload);
       } else if (e == hipSuccess && pinned_range_ok(v[i].payload, v[i].payload_bytes, attr)) {
-        kind[i] = 2;
+        // the unpack kernel reads it over the host link: one launch at 55.6 GB/s
+        // for any number of blocks (67 M parameters in 111 tensors 20.9 -> 16.8
+        // ms; a copy command per block and shadow takes turns with the link).
+        // Blocks of 80 MB and more would copy at 56.3-56.8 GB/s, but not always:
+        // with them copied, the 111 tensors took 17.5-18.0 ms in four processes
+        // of twenty, which had run other work before, and 16.7 in the others.
+        kind[i] = 0;
         dev_base[i] = static_cast<const uint8_t*>(attr.devicePointer);
       } else {
         (void)hipGetLastError();
@@ -880,8 +875,7 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
     uint64_t off = 0;
     for (uint32_t j = 0; j < l; ++j)
       if (v[i].mask[j]) off += L.rec_bytes[j];
-    const bool copied = kind[i] == 1 || (kind[i] == 2 && L.rec_bytes[l] >= kPinnedCopyBlock * L.layer_blocks(l));
-    if (!copied) {
+    if (kind[i] == 0) {
       ranks.push_back({reinterpret_cast<uint64_t>(dev_base[i] + off), pieces, L.layer_piece_begin[l], v[i].step});
       pieces += L.layer_pieces[l];
     } else {

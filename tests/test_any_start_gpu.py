@@ -228,45 +228,3 @@ def test_restore_of_any_number_of_layers(N):
         LC.lc_score_layers(ctx, 4)
     finally:
         LC.lc_destroy(ctx)
-
-
-@pytest.mark.parametrize("dtype,master", [("f32", False), ("bf16", True)])
-def test_restore_of_large_page_locked_blocks(dtype, master):
-    """Layers whose blocks have 32 MiB and more in the mean are copied, the others read by the kernel, in one restore; the
-    same from device memory, where the kernel reads all."""
-    import torch
-    wd = torch.float32 if dtype == "f32" else torch.bfloat16
-    sizes = [5, (16 << 20) + 3, 1001, (16 << 20) + 64]
-    n, at, segs = sum(sizes), 0, []
-    src = [((torch.arange(n, device="cuda") + 7 * k) % 251).to(wd if k == 0 else torch.float32) for k in range(3 + master)]
-    arr = {k: torch.zeros_like(src[0] if k in "ws" else src[1]) for k in "ws" + "M" * master + "mv"}
-    for l, k in enumerate(sizes):
-        p = {a: t.data_ptr() + at * t.element_size() for a, t in arr.items()}
-        segs.append(LC.Segment(l, k, p["w"], p["s"], p.get("M"), p["m"], p["v"]))
-        at += k
-    stream = torch.cuda.current_stream().cuda_stream
-    ctx = LC.lc_init_layout(LC.LayoutDesc(segs, 4, LC.LC_DT_F32 if dtype == "f32" else LC.LC_DT_BF16, master,
-                                          LC.LC_MODE_ACCUM, [1.0] * 4, s_max=9, stream=stream))
-    try:
-        rec = [LC.lc_record_bytes(ctx, l) for l in range(4)]
-        dev, off, at = torch.zeros(sum(rec), dtype=torch.uint8, device="cuda"), 0, 0
-        for l, k in enumerate(sizes):
-            for a in src:
-                b = a[at:at + k].view(torch.uint8)
-                dev[off:off + b.numel()] = b
-                off += -(-b.numel() // 256) * 256
-            at += k
-        pinned = torch.empty(sum(rec), dtype=torch.uint8, pin_memory=True)
-        pinned.copy_(dev)
-        for buf in (pinned, dev):
-            for t in arr.values():
-                t.fill_(-1.0)
-            v = [{"step": 3, "mask": np.ones(4, np.uint8), "payload": buf.data_ptr(), "payload_bytes": sum(rec)}]
-            assert LC.lc_restore_composite(ctx, v, 3, 4).tolist() == [3] * 4
-            for a, t in zip("w" + "M" * master + "mv", src):
-                assert torch.equal(arr[a], t), a
-            assert torch.equal(arr["s"], src[0])
-            _, delta, t_last = LC.lc_read_state(ctx, 4)
-            assert not delta.any() and t_last.tolist() == [3] * 4
-    finally:
-        LC.lc_destroy(ctx)

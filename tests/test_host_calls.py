@@ -118,20 +118,6 @@ def gradient_tables(n, fetches):
     assert w == ["query"] * (4 if fetches else 0) + first, w
 
 
-def restore_route(where, edge_copies):
-    import numpy as np
-    h = hip()
-    edge = (32 << 20) // 4
-    sizes = [edge - 64, 5, edge]  # the records' blocks are padded to 64 elements
-    LC, ctx = context(h, sizes)
-    rec = [LC.lc_record_bytes(ctx, l) for l in range(3)]
-    assert rec[2] == 3 * (32 << 20) and rec[0] == rec[2] - 3 * 256
-    v = [{"step": 0, "mask": np.ones(3, np.uint8), "payload": h.standin_alloc(sum(rec), where), "payload_bytes": sum(rec)}]
-    LC.lc_restore_composite(ctx, v, 0, 3)
-    w = ["unpack" if "unpack_kernel" in x else x for x in h.words() if "unpack" in x or x == "copy"]
-    assert w == ["unpack"] + ["copy"] * edge_copies, w
-
-
 # ---- the tests ---------------------------------------------------------------------------------------------------------
 
 
@@ -161,9 +147,3 @@ def test_a_gradient_table_waits_for_the_fetch_of_the_one_before(standin, n, fetc
     """Up to 224 segments the table rides in the kernel's arguments; beyond that the page-locked table may not be written
     while the fetch of the previous call is under way (beyond 1024 a second launch behind the fetch says that it is done)."""
     in_child(standin, LIB, "gradient_tables", n, fetches)
-
-
-@pytest.mark.parametrize("where,edge_copies", [(DEVICE, 0), (HOST, 4)], ids=["device", "page-locked"])
-def test_page_locked_layers_of_large_blocks_are_copied(standin, where, edge_copies):
-    """From 32 MiB a block on: three arrays and the shadow; smaller layers and device records go to the kernel."""
-    in_child(standin, LIB, "restore_route", where, edge_copies)
