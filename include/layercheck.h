@@ -73,9 +73,10 @@ typedef struct lc_ctx lc_ctx; /* opaque, library-owned */
 /* One contiguous piece of one tensor of one layer.  All arrays hold `numel`
  * elements; weight and shadow have the layout's weight dtype, the others are
  * fp32.  Pointers must be naturally aligned (2 B for bf16, 4 B for fp32); a
- * segment may start at any element, which costs 1-10% of the rate where its
- * arrays are not alike modulo 16 bytes.  No two arrays of a layout (over all
- * its segments) may overlap in memory: LC_ERR_INVALID_ARG. */
+ * segment may start at any element; where its arrays are not alike modulo 16
+ * bytes, calls take up to 10% longer, the score of LC_MODE_SNAPSHOT 16%.  No
+ * two arrays of a layout (over all its segments) may overlap in memory:
+ * LC_ERR_INVALID_ARG. */
 typedef struct {
   uint32_t layer;     /* layer group id in [0, n_layers)                      */
   uint32_t reserved;  /* must be 0                                            */

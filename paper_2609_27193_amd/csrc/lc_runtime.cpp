@@ -273,9 +273,11 @@ lc_status check_ctx(lc_ctx* c) {
 // synchronisation.  Now and then the stream is queried, so an error ends the
 // wait, and so does a stream that drained without the number (`drained`).  A
 // query takes microseconds and holds up the launch behind it, so there are
-// kPolls polls (about 50 us) between two: on 3.7 M parameters a decision step
-// takes 33.4 us and an AdamW step 42.7, with a query every 256 polls 36.6 and
-// 48.0.
+// kPolls polls (about 50 us) between two.  With a query every 256 polls against
+// every 64 K: a decision on 336 M parameters, its state read back, 512 -> 501
+// and 517 -> 505 us (runs of one side within 0.7%); a decision on 3.7 M has two
+// speeds with the former, 34-35 us in the mean, and 28.9 with the latter.  An
+// AdamW step on 3.7 M has two speeds 10 us apart with either.
 constexpr uint32_t kPolls = 1u << 16;
 
 hipError_t wait_number(lc_ctx* c, const uint64_t* number, uint64_t want, bool* drained) {
@@ -863,7 +865,7 @@ lc_status lc_restore_composite(lc_ctx* c, const lc_version* v, uint32_t n_versio
         // for any number of blocks (67 M parameters in 111 tensors 20.9 -> 16.8
         // ms; a copy command per block and shadow takes turns with the link).
         // Blocks of 80 MB and more would copy at 56.3-56.8 GB/s, but not always:
-        // with them copied, the 111 tensors took 17.5-18.0 ms in four processes
+        // with them copied, the 111 tensors took 17.5-18.1 ms in four processes
         // of twenty, which had run other work before, and 16.7 in the others.
         kind[i] = 0;
         dev_base[i] = static_cast<const uint8_t*>(attr.devicePointer);
