@@ -687,8 +687,8 @@ def main_restore(args, spec):
     many as device memory holds).  Timed with every version resident in
     device memory (the unpack kernel, against the HBM roofline) and, when the
     record set fits in 48 GB, with every version in pinned host memory
-    (per-block host-to-device copies, against a plain pinned copy as the
-    host-link ceiling).  Bytes: each layer's record read once, its arrays and
+    (the same kernel over the host link, against a plain pinned copy as the
+    link's ceiling).  Bytes: each layer's record read once, its arrays and
     its shadow written once."""
     import torch
     from paper_2609_27193_amd import inputs as I
