@@ -272,13 +272,14 @@ lc_status check_ctx(lc_ctx* c) {
 // of the kernel's store instead of after a device-to-host copy and a stream
 // synchronisation.  Now and then the stream is queried, so an error ends the
 // wait, and so does a stream that drained without the number (`drained`).  A
-// query takes microseconds and holds up the launch behind it, so there are
-// kPolls polls (about 50 us) between two.  With a query every 256 polls against
-// every 64 K: a decision on 336 M parameters, its state read back, 512 -> 501
-// and 517 -> 505 us (runs of one side within 0.7%); a decision on 3.7 M has two
-// speeds with the former, 34-35 us in the mean, and 28.9 with the latter.  An
-// AdamW step on 3.7 M has two speeds 10 us apart with either.
-constexpr uint32_t kPolls = 1u << 16;
+// query shortly before the number arrives holds up the launch behind it by up to
+// 18 us, so there are kPolls polls (about 3 ms) between two, where that is 0.6%.
+// Decisions, us, a query every 256 polls / 64 K (50 us) / none in the wait: 3.7 M
+// fp32 weights 34-35 / 28.9 / 28.9, 7 M 51.9 / 61.9 / 45.7, 14 M bf16 61.0 / 66.8 /
+// 52.0, 28 M 90.7 / 84.2 / 79.2, 40 M 110.4 / 100.3 / 98.8; 336 M bf16 with the state
+// read back 512-517 / 501-505.  An AdamW step on 3.7 M has two speeds 10 us apart
+// with each.
+constexpr uint32_t kPolls = 1u << 22;
 
 hipError_t wait_number(lc_ctx* c, const uint64_t* number, uint64_t want, bool* drained) {
   const volatile uint64_t* flag = number;
@@ -1057,7 +1058,9 @@ lc_status lc_read_state(lc_ctx* c, double* u_out, double* delta_out, int64_t* t_
   // A kernel behind all enqueued work writes the state into pinned memory.  The
   // call synchronises the stream, as it promises: 18.2 us on 200 layers, three
   // copies of the runtime behind a synchronisation 51; a number polled in its
-  // place 13.8, but then the stream may still be busy.
+  // place 13.8, but then the stream may still be busy.  Both cost more than the
+  // one (a decision with its log on 1 M parameters 40.5 us against 37.5), and so
+  // does a loop of queries (55).
   OnDevice on(c);
   LC_HIP(c, launch_push_state(c->dt, c->dev_h_state, c->stream));
   LC_HIP(c, hipStreamSynchronize(c->stream));

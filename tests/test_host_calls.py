@@ -104,6 +104,23 @@ def stale_error(where, n_layers):
     LC.lc_restore_composite(ctx, v, 0, n_layers)
 
 
+def selection_wait():
+    import time
+    h = hip()
+    LC, ctx = context(h, [3000])
+    LC.lc_score_layers(ctx, 1)
+    h.standin_clear()
+    t = time.perf_counter()
+    try:
+        LC.lc_select(ctx, 1, 1.0, 1)  # no kernel runs: the number never comes
+        raise AssertionError("no error")
+    except LC.LCError as e:
+        assert e.code == LC.LC_ERR_HIP
+    took = time.perf_counter() - t
+    w = [x for x in h.words() if x in ("query", "sync")]
+    assert w == ["query"] and took > 0.5e-3, (w, took)
+
+
 def gradient_tables(n, fetches):
     h = hip()
     LC, ctx = context(h, [1] * n)
@@ -132,6 +149,11 @@ def test_a_failed_restore_waits_for_what_it_launched(standin, n_layers, where):
 def test_reading_the_state_synchronises_the_stream(standin):
     """As the header promises: the stream is idle when the call returns."""
     in_child(standin, LIB, "state_read")
+
+
+def test_a_selection_is_polled_for_long_before_the_stream_is_queried(standin):
+    """A query just before the selection arrives holds up the pack; a stream that drains without it still ends the wait."""
+    in_child(standin, LIB, "selection_wait")
 
 
 @pytest.mark.parametrize("where", [HOST, 0], ids=["page-locked", "pageable"])
