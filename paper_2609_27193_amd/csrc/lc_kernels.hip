@@ -408,6 +408,11 @@ __global__ __launch_bounds__(kTableThreads) void reset_state_kernel(const Device
 // start anywhere: on a 160 M element layer with every array at an odd element
 // the pack takes 689 us (aligned 679; two bytes a lane took 891), with the
 // shadow refreshed 763 (726; 1415) and the restore 767 (767; 1454).
+// The restore reads a source that does not start on a line as one that starts
+// anywhere: a line that two waves share then comes once over the host link, while
+// the tiles' device scope fetches it twice.  Records in page-locked memory, arrays
+// 16 bytes off a line, W, m and v of 80 MB: 50.7 -> 56.9 GB/s (through copies 56.3;
+// arrays on a line 55.5); in device memory either way takes as long.
 template <bool ANYS, bool ANYD>
 __device__ __forceinline__ void copy_full_piece(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
                                                 uint8_t* __restrict__ dst2) {
@@ -436,10 +441,11 @@ __device__ __forceinline__ void copy_full_piece(const uint8_t* __restrict__ src,
   }
 }
 
+template <uint32_t SRC_ALIGN>
 __device__ __forceinline__ void copy_piece(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
                                            uint8_t* __restrict__ dst2, uint32_t len) {
   const uint32_t tid = threadIdx.x;
-  const bool any_s = reinterpret_cast<uint64_t>(src) % 16 != 0, any_d = reinterpret_cast<uint64_t>(dst2) % 16 != 0;
+  const bool any_s = reinterpret_cast<uint64_t>(src) % SRC_ALIGN != 0, any_d = reinterpret_cast<uint64_t>(dst2) % 16 != 0;
   uint32_t done = 0;
   if (reinterpret_cast<uint64_t>(dst) % 16 == 0) {
     if (len == kPieceBytes) {
@@ -496,7 +502,7 @@ __device__ __forceinline__ void pack_piece(const PackTables& t, uint32_t first, 
   uint8_t* dst = staging + (t.sel_rec_prefix[lo] - rec_base) + u.rec_off + off;
   const uint8_t* src = reinterpret_cast<const uint8_t*>(u.arr) + off;
   uint8_t* dst2 = (REFRESH && u.shadow) ? reinterpret_cast<uint8_t*>(u.shadow) + off : nullptr;
-  copy_piece(src, dst, dst2, len);
+  copy_piece<16>(src, dst, dst2, len);
   if (off + len == u.bytes) {  // zero the block's padding
     const uint32_t pad = static_cast<uint32_t>(round_up(u.bytes, kRecordAlign) - u.bytes);
     g_u16* z = (g_u16*)(dst + len);
@@ -538,11 +544,11 @@ __device__ __forceinline__ void unpack_piece(const UnpackArgs& t, const c_RankEn
   uint8_t* dst = reinterpret_cast<uint8_t*>(u.arr);
   uint8_t* dst2 = u.shadow ? reinterpret_cast<uint8_t*>(u.shadow) : nullptr;
   const uint32_t p = static_cast<uint32_t>(lp) - u.piece0;
-  if (p == 0 && u.head) copy_piece(src, dst, dst2, u.head);
+  if (p == 0 && u.head) copy_piece<kLineBytes>(src, dst, dst2, u.head);
   const uint64_t off = static_cast<uint64_t>(p) * kPieceBytes + u.head;
   const uint64_t rem = u.bytes > off ? u.bytes - off : 0;
   const uint32_t len = rem < kPieceBytes ? static_cast<uint32_t>(rem) : kPieceBytes;
-  if (len) copy_piece(src + off, dst + off, dst2 ? dst2 + off : nullptr, len);
+  if (len) copy_piece<kLineBytes>(src + off, dst + off, dst2 ? dst2 + off : nullptr, len);
 }
 
 // One piece per block, from piece_base on (split like the pack).  Ranks in the

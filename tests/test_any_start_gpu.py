@@ -228,3 +228,34 @@ def test_restore_of_any_number_of_layers(N):
         LC.lc_score_layers(ctx, 4)
     finally:
         LC.lc_destroy(ctx)
+
+
+@pytest.mark.parametrize("where", ["pinned", "device"])
+@pytest.mark.parametrize("place", [0, 2, 16, 64])
+@pytest.mark.parametrize("first", [0, 4, 5])
+def test_records_written_again_between_restores(first, place, where):
+    """Records at, beside and off a line, arrays too; the second restore reads what the host wrote into the same memory."""
+    import torch
+    n = 2 * 2048 + 77  # fp32: whole pieces and a tail
+    arrs = [torch.zeros(n + 64, device="cuda") for _ in range(4)]  # w, s, m, v
+    seg = LC.Segment(0, n, *(a.data_ptr() + 4 * first if a is not None else None for a in (*arrs[:2], None, *arrs[2:])))
+    ctx = LC.lc_init_layout(LC.LayoutDesc([seg], 1, LC.LC_DT_F32, False, LC.LC_MODE_ACCUM, [1.0], s_max=9,
+                                          stream=torch.cuda.current_stream().cuda_stream))
+    try:
+        size = LC.lc_record_bytes(ctx, 0)
+        host = torch.empty(size + 256, dtype=torch.uint8, pin_memory=True)
+        buf = host if where == "pinned" else torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        v = [{"step": 3, "mask": np.ones(1, np.uint8), "payload": buf.data_ptr() + place, "payload_bytes": size}]
+        rng = np.random.default_rng(first)
+        for _ in range(3):
+            rec = rng.integers(0, 2 ** 16, (3, size // 12), dtype=np.uint32)
+            host.numpy()[place:place + size] = rec.view(np.uint8).reshape(-1)
+            if where == "device":
+                buf.copy_(host)
+            assert LC.lc_restore_composite(ctx, v, 3, 1).tolist() == [3]
+            for a, r in zip(arrs, (rec[0], rec[0], rec[1], rec[2])):
+                got = a.cpu().numpy().view(np.uint32)
+                assert np.array_equal(got[first:first + n], r[:n])
+                assert not got[:first].any() and not got[first + n:].any()
+    finally:
+        LC.lc_destroy(ctx)
