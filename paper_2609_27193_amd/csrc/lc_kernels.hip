@@ -371,7 +371,17 @@ __global__ __launch_bounds__(NT) void select_kernel(const uint64_t* numel, const
 // one block, tells the host that the source may be written again.
 __global__ __launch_bounds__(kTableThreads) void fetch_kernel(const u32x4* src, u32x4* dst, uint32_t n, uint64_t* flag,
                                                               uint64_t seq) {
-  for (uint32_t i = blockIdx.x * kTableThreads + threadIdx.x; i < n; i += gridDim.x * kTableThreads) dst[i] = src[i];
+  constexpr uint32_t U = 4;  // loads in flight: one trip over the link for up to 1024 entries a block
+  const uint32_t stride = gridDim.x * kTableThreads;
+  for (uint32_t i = blockIdx.x * kTableThreads + threadIdx.x; i < n; i += U * stride) {
+    u32x4 x[U];
+#pragma unroll
+    for (uint32_t k = 0; k < U; ++k)
+      if (i + k * stride < n) x[k] = src[i + k * stride];
+#pragma unroll
+    for (uint32_t k = 0; k < U; ++k)
+      if (i + k * stride < n) dst[i + k * stride] = x[k];
+  }
   __syncthreads();  // every load has returned: its value was stored
   if (threadIdx.x == 0 && flag) *reinterpret_cast<volatile uint64_t*>(flag) = seq;
 }
@@ -671,11 +681,13 @@ static hipError_t launch_own(void (*kernel)(P...), uint32_t grid, uint32_t threa
 static uint32_t table_blocks(uint32_t n) { return std::min(kTableBlocks, (n + kTableThreads - 1) / kTableThreads); }
 
 // Beyond kOneBlockEntries the entries are shared out to several blocks and the
-// flag is set by a launch behind them, which costs 2 us and more than that is
-// saved (an SGD step of n segments as a C call, us, one block / several; a copy
-// command of the runtime): 600: 14.6 / 16.1, 15.5; 1500: 20.2 / 17.2, 31; 5000:
-// 53.7 / 34.8, 49; 20000: 186 / 103, 127; 100000: 941 / 524, 571.
-constexpr uint32_t kOneBlockEntries = 1024;
+// flag is set by a launch behind them, which costs 2 us and more (AdamW steps of
+// n segments of 40 fp32 elements, us, one step / four in a row, one block; several
+// blocks; a copy command of the runtime): 1300: 39.2 / 115; 40.6 / 123; 47.1 / 134;
+// 2000: 48.0 / 144; 49.7 / 155; 56.2 / 153; 3500: 71.9 / 210; 71.7 / 222; 78.8 / 218.
+// An SGD step as a C call, several blocks; copy: 5000: 34.8; 49; 20000: 103; 127;
+// 100000: 524; 571.
+constexpr uint32_t kOneBlockEntries = 4096;
 
 hipError_t launch_fetch(const void* host_src, void* dst, uint32_t n16, uint64_t* flag, uint64_t seq, hipStream_t st) {
   const bool one = flag && n16 <= kOneBlockEntries;

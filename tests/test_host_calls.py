@@ -164,8 +164,8 @@ def test_an_error_of_the_program_fails_no_state_read_or_restore(standin, n_layer
     in_child(standin, LIB, "stale_error", where, n_layers)
 
 
-@pytest.mark.parametrize("n,fetches", [(224, 0), (225, 1), (1024, 1), (1025, 2)])
+@pytest.mark.parametrize("n,fetches", [(224, 0), (225, 1), (4096, 1), (4097, 2)])
 def test_a_gradient_table_waits_for_the_fetch_of_the_one_before(standin, n, fetches):
     """Up to 224 segments the table rides in the kernel's arguments; beyond that the page-locked table may not be written
-    while the fetch of the previous call is under way (beyond 1024 a second launch behind the fetch says that it is done)."""
+    while the fetch of the previous call is under way (beyond 4096 a second launch behind the fetch says that it is done)."""
     in_child(standin, LIB, "gradient_tables", n, fetches)

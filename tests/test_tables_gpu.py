@@ -47,10 +47,10 @@ def test_state_of_every_layer(n):
 
 
 @pytest.mark.parametrize("opt", ["sgd", "adamw"])
-@pytest.mark.parametrize("n", [223, 224, 225, 300, 1024, 1025, 8193])
+@pytest.mark.parametrize("n", [223, 224, 225, 300, 1024, 1025, 4096, 4097, 8193])
 def test_gradient_tables_back_to_back(n, opt):
     """The gradients' addresses ride in the kernel's arguments up to 224 segments, beyond that in a page-locked table that
-    one block or, beyond 1024 segments, several fetch.  The steps follow each other with no read between them, behind a
+    one block or, beyond 4096 segments, several fetch.  The steps follow each other with no read between them, behind a
     stream that is still busy, each with other gradients and other decayed segments: a table that the next call writes too
     early, or that is not read whole, shows in the parameters."""
     import torch
