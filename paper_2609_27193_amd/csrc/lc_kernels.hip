@@ -594,10 +594,19 @@ void launch_score_t(const DeviceTables& t, hipStream_t st) {
   }
 }
 
+// A copy of many ranks waits for its search over them, a chain of loads that
+// more blocks hide better than the cap on them serves HBM: beyond kSearchRanks
+// none is held back (us, capped / not: pack of 240 ranks, 32 M elements 147.0 /
+// 140.7, 8 M 45.0 / 41.0, of 2400 179.6 / 154.5; restore of 300 layers, 40 M elements
+// 232.8 / 207.0; packs of up to 60 ranks gain 3% by the cap on large states).
+constexpr uint32_t kSearchRanks = 128;
+
+uint32_t copy_lds(uint32_t ranks) { return ranks > kSearchRanks ? 0 : occupancy_lds(LC_COPY_BLOCKS_PER_CU); }
+
 template <bool REFRESH>
 void launch_pack_t(const DeviceTables& t, uint32_t first, uint32_t last, uint64_t piece_base, uint64_t n_pieces,
                    uint64_t rec_base, uint8_t* stg, hipStream_t st) {
-  const uint32_t lds = occupancy_lds(LC_COPY_BLOCKS_PER_CU);
+  const uint32_t lds = copy_lds(last - first);
   for (uint64_t done = 0; done < n_pieces;) {
     const uint32_t g = grid_for(n_pieces - done, kCopyThreads);
     hipLaunchKernelGGL((pack_kernel<REFRESH>), dim3(g), dim3(kCopyThreads), lds, st, t.sel_piece_prefix, t.sel_layer,
@@ -726,7 +735,7 @@ hipError_t launch_unpack(const DeviceTables& t, const RankEntry* ranks, uint32_t
   a.n_ranks = n_ranks;
   a.pad = 0;
   if (ranks) std::copy(ranks, ranks + n_ranks + 1, a.inline_ranks);
-  const uint32_t lds = occupancy_lds(LC_COPY_BLOCKS_PER_CU);
+  const uint32_t lds = copy_lds(n_ranks);
   for (uint64_t done = 0; done < n_pieces;) {
     const uint32_t g = grid_for(n_pieces - done, kCopyThreads);
     a.piece_base = done;
