@@ -239,6 +239,7 @@ static_assert(sizeof(HostState) == 64, "tables stay 16-byte aligned");
 struct DeviceTables {
   uint32_t n_layers;
   uint32_t n_chunks;
+  uint64_t total_numel;
   int dtype;  // 1 bf16, 2 f32
   int mode;   // 0 accum, 1 snapshot
   double eps_w;

@@ -612,6 +612,7 @@ lc_status lc_init_layout(const lc_layout_desc* d, lc_ctx** out) {
   DeviceTables& t = c->dt;
   t.n_layers = N;
   t.n_chunks = static_cast<uint32_t>(L.chunk_seg.size());
+  t.total_numel = L.total_numel;
   t.dtype = L.dtype;
   t.mode = d->mode;
   t.eps_w = d->eps_w;
