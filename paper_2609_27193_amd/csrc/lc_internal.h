@@ -164,8 +164,8 @@ struct GradSeg {
 // The gradient table of a layout of up to kInlineGrads segments goes into the
 // kernel's arguments (their limit is 4 KiB): no table in memory, no launch to
 // fill it and no gap behind that (with select and pack, fetched table against
-// arguments: AdamW step on 3.7 M parameters in the slower of its two speeds 54.7
-// -> 52.3 us, SGD step on 336 M 747.7 -> 744.1).
+// arguments, three pairs: AdamW step on 3.7 M parameters 44.7-44.9 -> 41.4-42.2 us,
+// SGD step on 336 M 747 -> 742).
 constexpr uint32_t kInlineGrads = 224;
 struct InlineGrads {
   GradSeg g[kInlineGrads];

@@ -275,10 +275,10 @@ lc_status check_ctx(lc_ctx* c) {
 // query shortly before the number arrives holds up the launch behind it by up to
 // 18 us, so there are kPolls polls (about 3 ms) between two, where that is 0.6%.
 // Decisions, us, a query every 256 polls / 64 K (50 us) / none in the wait: 3.7 M
-// fp32 weights 34-35 / 28.9 / 28.9, 7 M 51.9 / 61.9 / 45.7, 14 M bf16 61.0 / 66.8 /
+// fp32 weights 37-39 / 28.9 / 28.6, 7 M 51.9 / 61.9 / 45.7, 14 M bf16 61.0 / 66.8 /
 // 52.0, 28 M 90.7 / 84.2 / 79.2, 40 M 110.4 / 100.3 / 98.8; 336 M bf16 with the state
-// read back 512-517 / 501-505.  An AdamW step on 3.7 M has two speeds 10 us apart
-// with each.
+// read back 512-517 / 501-505; AdamW step, select and pack on 3.7 M 46.2-46.8 / 42-54,
+// by whether the query fell into the wait's end / 41.4-42.2.
 constexpr uint32_t kPolls = 1u << 22;
 
 hipError_t wait_number(lc_ctx* c, const uint64_t* number, uint64_t want, bool* drained) {
